@@ -282,6 +282,14 @@ struct Raw<8> {
       __builtin_amdgcn_raw_buffer_store_b64(v.x, r, vo, so, 0);
   }
 };
+// A 16-byte store reads its data registers over several cycles, the last
+// lanes' last.  With the uniform offset in a scalar register the compiler
+// takes no wait state before the next vector instruction may overwrite them;
+// on gfx950 that instruction then reaches memory in lanes 60-63, now and then
+// (seen as wrong auxiliaries in an FP64 step where a select follows the store
+// directly).  The data registers are therefore held until
+// after a wait state.
+__device__ __forceinline__ void hold_store_data(u32x4 v) { asm volatile("s_nop 1" ::"v"(v)); }
 template <>
 struct Raw<16> {
   struct U { u32x4 x; };
@@ -293,6 +301,7 @@ struct Raw<16> {
       __builtin_amdgcn_raw_buffer_store_b128(v.x, r, vo, so, 2);
     else
       __builtin_amdgcn_raw_buffer_store_b128(v.x, r, vo, so, 0);
+    hold_store_data(v.x);
   }
 };
 template <>
