@@ -71,6 +71,12 @@ struct Coef2 {
   C ca, cb;
 };
 
+// CPML profile of one sample
+template <class C>
+struct alignas(4 * sizeof(C)) Prof {
+  C omb, a, kinv, pad;   // 1 - b, a, 1/kappa
+};
+
 // Kernel arguments.  Few base pointers (element offsets are derived in the
 // kernel) keep the scalar register file from spilling.
 template <class T, class C>
@@ -86,6 +92,7 @@ struct StepArgs {
   C* psh_out;               // H-side psi, new
   uint32_t psoff[6];        // element offset of the pair array holding each psi auxiliary
   const C* prof;            // CPML profiles [side E,H][axis][1 - b | a | 1/kappa][plen]
+  const Prof<C>* prof4;     // the same by sample: [side E,H][axis][plen]
   int32_t plen;
   const int32_t* seg;       // block index per cell: x [px] | y [ny] | z [nz]
   const Coef2<C>* coef;     // (Ca, Cb) per block [nsz][nsy][nsx]

@@ -23,6 +23,7 @@
 
 #include "../../include/yee.h"
 #include "yee_adjoint.hpp"
+#include "yee_direct.hpp"
 #include "yee_kernels.hpp"
 #include "yee_tb.hpp"
 
@@ -79,6 +80,7 @@ struct yee_ctx {
   int tb_req = 0, tb_ty_req = 0, tb_kz_req = 0;
   int tb_ty = 0, tb_kz = 0, tb_V = 0, tb_wpr = 1;
   bool tb_ok = false;
+  int direct_ty = 0;         // rows per tile of the no-march step (0: the march)
   size_t lds_limit = 65536;  // per-workgroup LDS, queried at bind time
 
   // host-side configuration
@@ -95,7 +97,7 @@ struct yee_ctx {
   bool bound = false;
   unsigned char* ws = nullptr;
   int64_t ws_bytes = 0;
-  Region fields[2], psi_e[2], psi_h[2], series, dft, stat, segr, coef, prof, pecplane, pecmask, rowflag,
+  Region fields[2], psi_e[2], psi_h[2], series, dft, stat, segr, coef, prof, prof4, pecplane, pecmask, rowflag,
       srcr, prober, freqr;
   size_t comp_bytes = 0;   // one component array
   size_t psi_len[6] = {};  // elements of each psi array (same for E and H side)
@@ -198,6 +200,7 @@ void layout(yee_ctx* c) {
   take(c->coef, (size_t)c->nsx * c->nsy * c->nsz * 2 * c->csize);
   c->prof_len = std::max({d.nx, d.ny, d.nz}) + 1;
   take(c->prof, 2 * 3 * 3 * c->prof_len * c->csize);
+  take(c->prof4, 2 * 3 * 4 * c->prof_len * c->csize);
   take(c->pecplane, (size_t)d.nz * 4);
   take(c->pecmask, c->pec_k.size() * (size_t)d.ny * c->px);
   take(c->rowflag, (size_t)d.nz * d.ny);
@@ -306,6 +309,7 @@ yee::StepArgs<T, C> fill_args(const yee_ctx* c, int V, int ty, int kz, bool reco
   a.psh_out = reinterpret_cast<C*>(c->ws + c->psi_h[nxt].off);
   for (int q = 0; q < 6; ++q) a.psoff[q] = c->psi_off[q];
   a.prof = reinterpret_cast<const C*>(c->ws + c->prof.off);
+  a.prof4 = reinterpret_cast<const Prof<C>*>(c->ws + c->prof4.off);
   a.plen = (int32_t)c->prof_len;
   a.seg = reinterpret_cast<const int32_t*>(c->ws + c->segr.off);
   a.coef = reinterpret_cast<const Coef2<C>*>(c->ws + c->coef.off);
@@ -397,14 +401,50 @@ yee_status launch_step_v(yee_ctx* c, hipStream_t s, bool record, const HistOut* 
   }
 }
 
+// The step without a march (yee_direct.hpp), one plane per workgroup.
+template <class T, class C, bool SEAM>
+yee_status launch_direct(yee_ctx* c, hipStream_t s, bool record, const HistOut* hist) {
+  using namespace yee;
+  StepArgs<T, C> a = fill_args<T, C>(c, 1, c->direct_ty, 1, record);
+  const int waves = (c->direct_ty + 1) * a.wpr + (a.nsrc > 0 ? 1 : 0);
+  const dim3 grid(a.ny_tiles, a.nz), block(kWave * waves);
+  const size_t lds = direct_lds_bytes_for(c->direct_ty, a.wpr, sizeof(C));
+  if (waves > kMaxBlockWaves || lds > c->lds_limit) return fail(YEE_EINVAL, "no-march tile of %d rows does not fit", c->direct_ty);
+  if constexpr (std::is_same<T, C>::value) {
+    if (hist) {
+      a.hist = static_cast<T*>(hist->dst);
+      a.hstride = hist->stride;
+      for (int q = 0; q < 6; ++q) a.hbox[q] = hist->box[q];
+      hipLaunchKernelGGL((direct_kernel<T, C, SEAM, kHistory>), grid, block, lds, s, a);
+      HIP_TRY(hipGetLastError());
+      return YEE_OK;
+    }
+  }
+  if (c->dbg_count) {
+    a.wcount = c->dbg_count;
+    hipLaunchKernelGGL((direct_kernel<T, C, SEAM, kWriteCount>), grid, block, lds, s, a);
+  } else {
+    hipLaunchKernelGGL((direct_kernel<T, C, SEAM>), grid, block, lds, s, a);
+  }
+  HIP_TRY(hipGetLastError());
+  return YEE_OK;
+}
+
+template <class T, class C>
+yee_status launch_single(yee_ctx* c, hipStream_t s, bool record, const HistOut* hist) {
+  if (c->direct_ty == 0) return launch_step_v<T, C>(c, s, record, hist);
+  return c->d.nx > yee::kWave ? launch_direct<T, C, true>(c, s, record, hist)
+                              : launch_direct<T, C, false>(c, s, record, hist);
+}
+
 // One single step; hist (FP64 and FP32 contexts only) also writes E^{n+1} of a box.
 yee_status launch_one_step(yee_ctx* c, hipStream_t s, bool record = true, const HistOut* hist = nullptr) {
   switch (c->d.precision) {
-    case YEE_F64: return launch_step_v<double, double>(c, s, record, hist);
-    case YEE_F32: return launch_step_v<float, float>(c, s, record, hist);
+    case YEE_F64: return launch_single<double, double>(c, s, record, hist);
+    case YEE_F32: return launch_single<float, float>(c, s, record, hist);
     default:
       if (hist) return fail(YEE_EINVAL, "box history is written for FP64 and FP32 contexts only");
-      return launch_step_v<_Float16, float>(c, s, record, nullptr);
+      return launch_single<_Float16, float>(c, s, record, nullptr);
   }
 }
 
@@ -599,6 +639,26 @@ void tb_default_launch(yee_ctx* c) {
   c->tb_ok = true;
 }
 
+// Rows per tile of the no-march step, 0 where the march is faster or the
+// caller chose a launch shape.  The line lies at 4 MiB of one component in
+// compute precision, rows padded to whole waves (idle lanes cost the same).
+// Measured per step, march against no march (us): FP32 64^3 12.4 / 8.1,
+// 128 x 64 x 64 17.1 / 13.1, 64 x 96 x 96 18.3 / 12.6, 80^3 20.2 / 17.5 (below
+// the line); 96^3 22.6 / 23.9, FP64 80^3 27.3 / 29.1 (above it); FP64 64^3
+// 16.2 / 11.3.  Four rows: two to seven were within a few percent, three and
+// seven the slowest.
+constexpr int64_t kDirectMaxBytes = int64_t(4) << 20;
+constexpr int kDirectRows = 4;
+
+int direct_rows(const yee_ctx* c) {
+  const auto& d = c->d;
+  if (c->ty_req || c->kz_req || c->vpl || d.nz > 65535) return 0;
+  const int wpr = waves_per_row(d.nx, 1);
+  if ((int64_t)wpr * yee::kWave * d.ny * d.nz * (int64_t)c->csize > kDirectMaxBytes) return 0;
+  // (a wave of the workgroup is the sources')
+  return std::max(0, std::min({kDirectRows, d.ny, (yee::kMaxBlockWaves - 1) / wpr - 1}));
+}
+
 void default_launch(yee_ctx* c) {
   const auto& d = c->d;
   c->V = c->vpl ? c->vpl : default_samples_per_lane(d);
@@ -637,6 +697,7 @@ void default_launch(yee_ctx* c) {
     if (c->ty == 1 || step_lds_bytes(c, c->ty, c->V, c->kz) <= c->lds_limit) break;
     --c->ty;
   }
+  c->direct_ty = direct_rows(c);
   tb_default_launch(c);
 }
 
@@ -995,9 +1056,10 @@ yee_status yee_launch_info(const yee_ctx* c, int32_t* steps_per_sweep, int32_t* 
   if (!c || !steps_per_sweep || !tile_rows || !chunk_planes || !samples_per_lane) return fail(YEE_EINVAL, "NULL argument");
   if (!c->bound) return fail(YEE_ESTATE, "no workspace bound");
   *steps_per_sweep = c->tb_ok ? 2 : 1;
-  *tile_rows = c->tb_ok ? c->tb_ty : c->ty;
-  *chunk_planes = c->tb_ok ? c->tb_kz : c->kz;
-  *samples_per_lane = c->tb_ok ? c->tb_V : c->V;
+  const bool direct = !c->tb_ok && c->direct_ty > 0;
+  *tile_rows = c->tb_ok ? c->tb_ty : direct ? c->direct_ty : c->ty;
+  *chunk_planes = c->tb_ok ? c->tb_kz : direct ? 1 : c->kz;
+  *samples_per_lane = c->tb_ok ? c->tb_V : direct ? 1 : c->V;
   return YEE_OK;
 }
 
@@ -1028,7 +1090,7 @@ yee_status yee_reset(yee_ctx* c, void* stream) {
   yee_status st = upload_materials_impl(c, s);
   if (st) return st;
   // CPML profiles
-  std::vector<unsigned char> pbuf(c->prof.bytes, 0);
+  std::vector<unsigned char> pbuf(c->prof.bytes, 0), pbuf4(c->prof4.bytes, 0);
   const int n3[3] = {d.nx, d.ny, d.nz};
   const double dw[3] = {d.dx, d.dy, d.dz};
   for (int side = 0; side < 2; ++side)
@@ -1042,8 +1104,15 @@ yee_status yee_reset(yee_ctx* c, void* stream) {
       } else {
         put<float>(pbuf, base, b); put<float>(pbuf, base + c->prof_len * 4, a); put<float>(pbuf, base + 2 * c->prof_len * 4, k);
       }
+      std::vector<double> by_sample(4 * c->prof_len, 0.0);
+      for (size_t q = 0; q < c->prof_len; ++q) {
+        by_sample[4 * q] = b[q]; by_sample[4 * q + 1] = a[q]; by_sample[4 * q + 2] = k[q];
+      }
+      const size_t base4 = (size_t)(side * 3 + ax) * 4 * c->prof_len * c->csize;
+      if (c->csize == 8) put<double>(pbuf4, base4, by_sample); else put<float>(pbuf4, base4, by_sample);
     }
   if ((st = upload(c, c->prof, pbuf.data(), pbuf.size(), s))) return st;
+  if ((st = upload(c, c->prof4, pbuf4.data(), pbuf4.size(), s))) return st;
   // PEC planes
   std::vector<int32_t> plane(d.nz, -1);
   std::vector<uint8_t> masks(c->pecmask.bytes, 0);
