@@ -20,7 +20,7 @@
 //                  products of phasor tiles split into fp16 high and low parts
 //                  (fast time factored into 32 rows x 16 columns).
 //   reduce_kernel  sums synth_kernel's partition cubes in FP64, fixed order.
-//   fft_kernel     radix-2 FFT of lines held in LDS (Eq. 4, one axis a pass).
+//   fft_kernel     FFT of lines, 8 elements a thread (Eq. 4, one axis a pass).
 //   span_kernel    Eq. 5 rule masks, one thread per ray.
 //   check_kernel   counts rays with out-of-range meta data.
 #include <hip/hip_runtime.h>
@@ -728,60 +728,147 @@ __global__ void reduce_kernel(const float2* __restrict__ partial, float2* __rest
     s[((int64_t)q * n_chirps_out + c0 + jj) * n_samples + n] = make_float2((float)re, (float)im);
 }
 
-// Radix-2 decimation-in-time FFT of `lines` lines of length L = 2^logL, M
-// lines per workgroup held in LDS.  Line m starts at
-//   (m / per_group) * group_stride + (m % per_group) * line_stride
-// and its elements are elem_stride apart.  Twiddles exp(-2 pi i k / L) are
-// formed in FP64 and rounded once.
-__global__ __launch_bounds__(256) void fft_kernel(const float2* in, float2* out, int logL, int lines, int M,
-                                                  int per_group, int64_t group_stride, int64_t line_stride,
-                                                  int64_t elem_stride) {
+// FFT of lines of length L = 2^LOGL (Eq. 4, one axis a pass), in place or not:
+// a Stockham autosort transform with E = min(8, L) elements of a line in each
+// thread's registers.  The first stage (radix 2, 4 or 8, what L leaves over
+// powers of 8) takes its elements straight from memory and the last one writes
+// straight back, both in natural order; the radix-8 stages between them
+// exchange through LDS, log8 L - 1 times.  Twiddles exp(-2 pi i k / L), k < L/2,
+// are formed in FP64 and rounded once, after the loads are under way.
+//
+// What bounds it is latency, not the 16 bytes per sample of traffic: a radix-2
+// transform in LDS paid two barriers and two LDS round trips for each of its
+// log2 L stages and started from bit-reversed LDS writes.  12 x 128 x 512
+// samples took 35 us for both passes of that and take 12 here, 12 x 512 x 1024
+// 133 and 46 (2.2 TB/s); calls of 12 us are bound by the host.
+//
+// STRIDED: the elements of a line are 2^lg apart and lines m, m + 1, ... are
+// neighbours in memory (2^lg of them a group): lanes run over the lines, and the
+// LDS holds a line's elements LB apart.  Otherwise lines are contiguous, lanes
+// run along them, and the LDS pads every 8 elements by one (the stages' strides
+// of 8 would fall on a quarter of the banks).
+__device__ inline float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
+__device__ inline float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
+__device__ inline float2 mul_mi(float2 a) { return make_float2(a.y, -a.x); }   // times -i
+
+__device__ inline void dft2(float2& a, float2& b) {
+    const float2 t = csub(a, b);
+    a = cadd(a, b);
+    b = t;
+}
+__device__ inline void dft4(float2& a, float2& b, float2& c, float2& d) {     // outputs 0, 1, 2, 3 in a, b, c, d
+    dft2(a, c);
+    dft2(b, d);
+    d = mul_mi(d);
+    dft2(a, b);
+    dft2(c, d);
+    const float2 t = b;
+    b = c;
+    c = t;
+}
+
+template <int R>
+__device__ inline void dft(float2 (&v)[R]) {
+    if constexpr (R == 2) {
+        dft2(v[0], v[1]);
+    } else if constexpr (R == 4) {
+        dft4(v[0], v[1], v[2], v[3]);
+    } else if constexpr (R == 8) {
+        dft4(v[0], v[2], v[4], v[6]);
+        dft4(v[1], v[3], v[5], v[7]);
+        constexpr float h = 0.70710678118654752f;
+        v[3] = make_float2(h * (v[3].x + v[3].y), h * (v[3].y - v[3].x));
+        v[5] = mul_mi(v[5]);
+        v[7] = make_float2(h * (v[7].y - v[7].x), -h * (v[7].x + v[7].y));
+#pragma unroll
+        for (int k = 0; k < 8; k += 2) dft2(v[k], v[k + 1]);
+        // (pairs k, k + 4) to natural order
+        const float2 a1 = v[1], a2 = v[2], a3 = v[3], a4 = v[4], a5 = v[5], a6 = v[6];
+        v[1] = a2; v[2] = a4; v[3] = a6; v[4] = a1; v[5] = a3; v[6] = a5;
+    }
+}
+
+template <int LOGL>
+struct FftPlan {
+    static constexpr int L = 1 << LOGL;
+    static constexpr int E = L < 8 ? L : 8;            // elements per thread
+    static constexpr int TPL = L / E;                  // threads per line
+    static constexpr int R0 = LOGL < 3 ? L : (LOGL % 3 == 0 ? 8 : LOGL % 3 == 1 ? 2 : 4);   // first radix
+};
+
+// The stages from NS = product of the radices done: v[q] holds element
+// t + q TPL.  at(e): LDS place of the line's element e; put(e, v): the result.
+template <int LOGL, int NS, int R, class At, class Put>
+__device__ inline void fft_stages(float2 (&v)[FftPlan<LOGL>::E], float2* lds, const float2* tw, int t, At&& at,
+                                  Put&& put) {
+    using P = FftPlan<LOGL>;
+    constexpr int NB = P::E / R;                       // butterflies of a thread
+    constexpr bool last = NS * R == P::L;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int j = t + b * P::TPL;
+        float2 u[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) u[r] = v[b + r * NB];
+        if constexpr (NS > 1) {
+            const int step = (j & (NS - 1)) * (P::L / (NS * R));
+#pragma unroll
+            for (int r = 1; r < R; ++r) {
+                const int k = r * step;                // < L
+                const float2 w = tw[k & (P::L / 2 - 1)];
+                const float sg = (k & (P::L / 2)) ? -1.0f : 1.0f;
+                u[r] = cmul(u[r], make_float2(sg * w.x, sg * w.y));
+            }
+        }
+        dft<R>(u);
+        const int d = (j / NS) * NS * R + (j & (NS - 1));
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if constexpr (last) put(d + r * NS, u[r]);
+            else lds[at(d + r * NS)] = u[r];
+        }
+    }
+    if constexpr (!last) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < P::E; ++q) v[q] = lds[at(t + q * P::TPL)];
+        if constexpr (NS * R * 8 < P::L) __syncthreads();   // the next stage writes these places again
+        fft_stages<LOGL, NS * R, 8>(v, lds, tw, t, at, put);
+    }
+}
+
+template <int LOGL, bool STRIDED>
+__global__ __launch_bounds__(1024) void fft_kernel(const float2* in, float2* out, int lines, int lg) {
+    using P = FftPlan<LOGL>;
+    constexpr int L = P::L, E = P::E, TPL = P::TPL;
     extern __shared__ float2 lds[];
-    const int L = 1 << logL;
-    float2* tw = lds;              // L / 2 twiddles
-    float2* x = lds + L / 2;       // M lines
-    for (int k = threadIdx.x; k < L / 2; k += blockDim.x) {
-        double sn, cs;
-        sincospi(-2.0 * k / L, &sn, &cs);
-        tw[k] = make_float2((float)cs, (float)sn);
-    }
-    const int m0 = blockIdx.x * M;
-    const int nm = min(M, lines - m0);
-    // load, bit-reversed within each line.  Consecutive threads take
-    // consecutive elements of a contiguous line, or the same element of
-    // neighbouring lines when the elements are strided.
-    const bool by_elem = elem_stride == 1;
-    for (int t = threadIdx.x; t < nm * L; t += blockDim.x) {
-        const int ml = by_elem ? t / L : t % nm, e = by_elem ? t % L : t / nm;
-        const int m = m0 + ml;
-        const int64_t base = (int64_t)(m / per_group) * group_stride + (int64_t)(m % per_group) * line_stride;
-        const int rev = logL ? (int)(__brev((unsigned)e) >> (32 - logL)) : 0;
-        x[ml * L + rev] = in[base + (int64_t)e * elem_stride];
-    }
-    __syncthreads();
-    for (int s = 0; s < logL; ++s) {
-        const int half = 1 << s;
-        for (int t = threadIdx.x; t < nm * (L / 2); t += blockDim.x) {
-            const int ml = t / (L / 2), k = t % (L / 2);
-            const int pos = k & (half - 1);
-            const int i0 = ((k >> s) << (s + 1)) + pos;
-            const int i1 = i0 + half;
-            const float2 w = tw[pos << (logL - 1 - s)];
-            float2* xl = x + ml * L;
-            const float2 u = xl[i0], v = xl[i1];
-            const float vr = v.x * w.x - v.y * w.y;
-            const float vi = v.x * w.y + v.y * w.x;
-            xl[i0] = make_float2(u.x + vr, u.y + vi);
-            xl[i1] = make_float2(u.x - vr, u.y - vi);
+    float2* tw = lds;                                  // L / 2 twiddles (L > 8)
+    float2* x = lds + (L > 8 ? L / 2 : 0);
+    const int LB = blockDim.x / TPL;                   // lines per workgroup
+    const int ln = STRIDED ? threadIdx.x % LB : threadIdx.x / TPL;
+    const int t = STRIDED ? threadIdx.x / LB : threadIdx.x % TPL;
+    const int m = blockIdx.x * LB + ln;
+    const bool ok = m < lines;
+    const int64_t base = STRIDED ? ((int64_t)(m >> lg) << (lg + LOGL)) + (m & ((1 << lg) - 1)) : (int64_t)m << LOGL;
+    const int es = STRIDED ? lg : 0;                   // log2 of the element stride
+    float2 v[E];
+#pragma unroll
+    for (int q = 0; q < E; ++q) v[q] = ok ? in[base + ((int64_t)(t + q * TPL) << es)] : make_float2(0.f, 0.f);
+    if constexpr (L > 8) {
+        for (int k = threadIdx.x; k < L / 2; k += blockDim.x) {
+            double sn, cs;
+            sincospi(-2.0 * k / L, &sn, &cs);
+            tw[k] = make_float2((float)cs, (float)sn);
         }
         __syncthreads();
     }
-    for (int t = threadIdx.x; t < nm * L; t += blockDim.x) {
-        const int ml = by_elem ? t / L : t % nm, e = by_elem ? t % L : t / nm;
-        const int m = m0 + ml;
-        const int64_t base = (int64_t)(m / per_group) * group_stride + (int64_t)(m % per_group) * line_stride;
-        out[base + (int64_t)e * elem_stride] = x[ml * L + e];
-    }
+    const int place = STRIDED ? ln : ln * (L + L / 8);
+    auto at = [&](int e) { return STRIDED ? e * LB + place : place + e + (e >> 3); };
+    auto put = [&](int e, float2 w) {
+        if (ok) out[base + ((int64_t)e << es)] = w;
+    };
+    if constexpr (LOGL == 0) put(0, v[0]);
+    else fft_stages<LOGL, 1, P::R0>(v, x, tw, t, at, put);
 }
 
 __global__ void span_kernel(rmd_scene sc, const uint8_t* __restrict__ in_set, rmd_span_rule rule,
@@ -1180,6 +1267,29 @@ rmd_status run_batches(const Plan& p, rmd::SynthArgs a, int32_t chirp0, int32_t 
     return RMD_OK;
 }
 
+// One pass of the range-Doppler transform over `lines` lines of 2^LOGL samples
+// (lg: log2 of the element stride of a strided pass).  Workgroups of 256
+// threads, or of 128 while that leaves compute units idle; strided lines want
+// at least 8 neighbours in a workgroup (64 bytes of each row), up to 1024
+// threads.
+template <bool STRIDED, int LOGL>
+void launch_fft_l(const float2* in, float2* out, int lines, int lg, hipStream_t stream) {
+    using P = rmd::FftPlan<LOGL>;
+    int threads = std::max(256, P::TPL);
+    if (STRIDED) threads = std::min(1024, std::max(threads, 8 * P::TPL));
+    else if (P::TPL <= 128 && (int64_t)lines * P::TPL < 512 * 256) threads = 128;
+    const int lb = threads / P::TPL;
+    const size_t words = (P::L > 8 ? P::L / 2 : 0) + (size_t)lb * (STRIDED ? P::L : P::L + P::L / 8);
+    hipLaunchKernelGGL((rmd::fft_kernel<LOGL, STRIDED>), dim3((lines + lb - 1) / lb), dim3(threads),
+                       P::L > 8 ? words * sizeof(float2) : 0, stream, in, out, lines, lg);
+}
+
+template <bool STRIDED, int LOGL = 0>
+void launch_fft(const float2* in, float2* out, int logl, int lines, int lg, hipStream_t stream) {
+    if (logl == LOGL) launch_fft_l<STRIDED, LOGL>(in, out, lines, lg, stream);
+    else if constexpr ((1 << LOGL) < RMD_MAX_FFT) launch_fft<STRIDED, LOGL + 1>(in, out, logl, lines, lg, stream);
+}
+
 // Resolves the hits into a.hit_rec once per call (both methods).
 rmd_status resolve_hits(const rmd::SynthArgs& a, hipStream_t stream) {
     if (a.n_hits > 0)
@@ -1289,22 +1399,9 @@ rmd_status rmd_range_doppler(const float* s, float* S, int32_t n_pairs, int32_t 
     auto lg = [](int32_t n) { int l = 0; while ((1 << l) < n) ++l; return l; };
     const auto* in = reinterpret_cast<const float2*>(s);
     auto* out = reinterpret_cast<float2*>(S);
-    // fast time: lines of n_samples, contiguous
-    {
-        const int L = n_samples, lines = n_pairs * n_chirps;
-        const int M = std::max(1, std::min(lines, 2048 / L));
-        const size_t lds = (size_t)(L / 2 + M * L) * sizeof(float2);
-        hipLaunchKernelGGL(rmd::fft_kernel, dim3((lines + M - 1) / M), dim3(256), lds, stream, in, out, lg(L),
-                           lines, M, 1, (int64_t)L, (int64_t)0, (int64_t)1);
-    }
-    // slow time: lines of n_chirps, n_samples apart; M neighbouring lines per block
-    {
-        const int L = n_chirps, lines = n_pairs * n_samples;
-        const int M = std::max(1, std::min(n_samples, 2048 / L));
-        const size_t lds = (size_t)(L / 2 + M * L) * sizeof(float2);
-        hipLaunchKernelGGL(rmd::fft_kernel, dim3((lines + M - 1) / M), dim3(256), lds, stream, out, out, lg(L),
-                           lines, M, n_samples, (int64_t)n_chirps * n_samples, (int64_t)1, (int64_t)n_samples);
-    }
+    // fast time: contiguous lines; slow time: lines n_samples apart, in place
+    launch_fft<false>(in, out, lg(n_samples), n_pairs * n_chirps, 0, stream);
+    launch_fft<true>(out, out, lg(n_chirps), n_pairs * n_samples, lg(n_samples), stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "fft_kernel launch");
     return RMD_OK;
