@@ -680,22 +680,36 @@ void default_launch(yee_ctx* c) {
   c->ty = c->ty_req ? c->ty_req
                     : std::max(1, std::min({tiny ? 2 : (wpr == 2 ? 4 : 7), d.ny, 12 / wpr - 1,
                                             yee::max_block_waves(c->V) / wpr - 1}));
+  // planes per chunk: the fewest (at least min_chunk) that let every tile be
+  // resident at once, so the launch runs in one round and each chunk pays its
+  // warm-up plane once over as long a march as possible
+  auto chunk_planes = [&](int ty) {
+    if (c->kz_req > 0) return std::min(c->kz_req, d.nz);
+    const int threads = (ty + 1) * wpr * yee::kWave;
+    const int slots = step_slots(c, threads, step_lds_bytes(c, ty, c->V, d.nz));
+    const int chunks = std::max(1, slots / ((d.ny + ty - 1) / ty));
+    return std::min({d.nz, kMaxChunk, std::max(min_chunk, (d.nz + chunks - 1) / chunks)});
+  };
   for (;;) {
-    if (c->kz_req > 0) {
-      c->kz = std::min(c->kz_req, d.nz);
-    } else {
-      // planes per chunk: the fewest (at least min_chunk) that let every
-      // tile be resident at once, so the launch runs in one round and each
-      // chunk pays its warm-up plane once over as long a march as possible
-      const int threads = (c->ty + 1) * wpr * yee::kWave;
-      const int slots = step_slots(c, threads, step_lds_bytes(c, c->ty, c->V, d.nz));
-      const int ny_tiles = (d.ny + c->ty - 1) / c->ty;
-      const int chunks = std::max(1, slots / ny_tiles);
-      c->kz = std::min({d.nz, kMaxChunk, std::max(min_chunk, (d.nz + chunks - 1) / chunks)});
-    }
+    c->kz = chunk_planes(c->ty);
     // keep the LDS rows and z tables within the device's per-workgroup limit
     if (c->ty == 1 || step_lds_bytes(c, c->ty, c->V, c->kz) <= c->lds_limit) break;
     --c->ty;
+  }
+  // FP64 steps take 128 VGPRs: a CU holds 16 waves, so one 12-wave workgroup
+  // and four idle slots.  Rows of three and four waves may take all 16 where
+  // the shorter march of the larger tile outweighs its slower planes (a plane
+  // takes about 8 + waves units).  us per step, 12 waves and up to 16:
+  // 150 x 130 x 110 85.8 / 78.0, 160^3 150.8 / 128.6, 200 x 200 x 100 182.9 /
+  // 152.6 (larger taken); 256 x 256 x 64 141.8 / 167.5 (not taken).
+  const int wide = yee::max_block_waves(c->V) / wpr - 1;
+  if (d.precision == YEE_F64 && c->V == 1 && wpr >= 3 && !tiny && !c->ty_req && wide > c->ty && wide <= d.ny) {
+    const int kz = chunk_planes(wide);
+    auto cost = [&](int ty, int planes) { return (planes + 1) * (8 + (ty + 1) * wpr); };
+    if (cost(wide, kz) < cost(c->ty, c->kz) && step_lds_bytes(c, wide, c->V, kz) <= c->lds_limit) {
+      c->ty = wide;
+      c->kz = kz;
+    }
   }
   c->direct_ty = direct_rows(c);
   tb_default_launch(c);
