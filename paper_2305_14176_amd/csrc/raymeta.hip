@@ -2,18 +2,19 @@
 // for gfx950.  The C ABI is declared in include/raymeta.h.
 //
 // Kernels:
-//   resolve_kernel each hit's triangle and vertex indices range-checked and
-//                  reduced to a record, once per call.
+//   prep_kernel    once per call: each hit's triangle and vertex indices
+//                  range-checked and reduced to a record; for rmd_if_cube also
+//                  the largest weight (sets the fixed-point scale) and the
+//                  spreading kernel's Fourier transform at the output
+//                  frequencies (FP64 quadrature).
 //   geometry_kernel Eq. 6 for every hit of a ray and the pair-independent
-//                  part of its path (FP64), once per ray and chirp.
+//                  part of its path (FP64), once per ray and chirp; in small
+//                  calls also prep_kernel's work.
 //   spread_kernel  Eqs. 7, 1, 2 (rmd_if_cube): per workgroup one antenna pair,
 //                  one chirp and one partition of the rays; the antenna legs
 //                  and phases per ray in FP64, then each ray's phasor spread
 //                  onto an oversampled periodic grid in LDS (the sum over rays
 //                  as a type-1 non-uniform FFT), in 64-bit fixed point.
-//   wmax_kernel    the largest weight (sets the fixed-point scale).
-//   deconv_kernel  the spreading kernel's Fourier transform at the output
-//                  frequencies (FP64 quadrature), once per call.
 //   finish_kernel  per (pair, chirp): the partitions' grids summed in FP64,
 //                  their inverse DFT (FP64, LDS) and the deconvolved samples.
 //   synth_kernel   the same sum evaluated directly (rmd_if_cube_direct): MFMA
@@ -111,8 +112,9 @@ struct SynthArgs {
     double cyc_per_m;           // f_c / c: carrier cycles per metre of path (Eq. 1 into Eq. 2)
     double step_per_m;          // mu / (c f_s): beat cycles per sample per metre (Eqs. 1-3)
     // spreading method: partial holds [n_parts][n_pairs][chirp_count][M] grids
-    const double* deconv;       // [n_samples]: 1 / psi_hat((n - center) / M)
-    const unsigned* wmax_bits;  // max_i |w_i| as float bits (1 when weights is NULL)
+    double* deconv;             // [n_samples]: 1 / psi_hat((n - center) / M)
+    unsigned* wmax_bits;        // [n_wmax]: partial maxima of |w_i| as float bits
+    int32_t n_wmax;             // at most kWave (0: every weight is 1)
     int32_t grid_log2, center;  // M = 2^grid_log2; center n_c = n_samples / 2
     // Tap t < kTaps / 2 has the polynomial P_t(s) = E_t(s^2) + s O_t(s^2), s in
     // [-1/2, 1/2); psi is even, so tap kTaps - 1 - t is P_t(-s) = E_t - s O_t.
@@ -167,11 +169,9 @@ __device__ inline bool hit_point(const SynthArgs& a, const double* __restrict__ 
     return true;
 }
 
-// Each hit resolved once per call: the vertex indices of its triangle and its
-// barycentric coordinates, or i1 = -1 if any index of the hit is out of range.
-__global__ void resolve_kernel(SynthArgs a) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= a.n_hits) return;
+// Hit k resolved: the vertex indices of its triangle and its barycentric u, or
+// i1 = -1 if any index of the hit is out of range.
+__device__ inline int4 resolve_hit(const SynthArgs& a, int64_t k) {
     int4 r = make_int4(-1, 0, 0, 0);
     const int32_t m = a.hit_mesh[k];
     if (m >= 0 && m < a.n_meshes) {
@@ -185,7 +185,65 @@ __global__ void resolve_kernel(SynthArgs a) {
                 r = make_int4(i1, i2, i3, __float_as_int(a.hit_u[k]));
         }
     }
-    a.hit_rec[k] = r;
+    return r;
+}
+
+// The tables of a call, by blocks of kPrepThreads threads: its deconvolution
+// factors and its largest weight (spreading method only).
+constexpr int kPrepThreads = 256;
+
+// deconv[n] = 1 / psi_hat((n - center) / M), psi_hat(xi) the integral of
+// psi(u) cos(2 pi xi u) over the kernel's support |u| <= kTaps / 2 (psi is
+// even), by the trapezoid rule with kQuad intervals in FP64 (psi falls to
+// e^{-beta} at the ends of its support, where the rule's error vanishes with
+// it).  One wave per n; the lanes' partial sums are combined in a fixed order.
+__device__ inline void deconv_block(const SynthArgs& a, int block) {
+    const int n = block * (kPrepThreads / kWave) + (int)(threadIdx.x / kWave);
+    const int lane = threadIdx.x & (kWave - 1);
+    if (n >= a.n_samples) return;
+    const double xi = (double)(n - a.center) / (double)(1 << a.grid_log2);
+    const double h = (double)kTaps / kQuad;
+    double acc = 0.0;
+    for (int i = lane; i <= kQuad; i += kWave) {
+        const double u = -0.5 * kTaps + i * h;
+        const double z = 2.0 * u / kTaps;
+        const double psi = exp(kBeta * (sqrt(fmax(0.0, 1.0 - z * z)) - 1.0));
+        acc += ((i == 0 || i == kQuad) ? 0.5 * h : h) * psi * cospi(2.0 * xi * u);
+    }
+    for (int off = kWave / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if (lane == 0) a.deconv[n] = 1.0 / acc;
+}
+
+// The float bits of max |w_i| over the block's share of the rays (nonnegative
+// floats order like their bit patterns).
+__device__ inline void wmax_block(const SynthArgs& a, int block) {
+    __shared__ unsigned wave_max[kPrepThreads / kWave];
+    unsigned m = 0u;
+    for (int64_t i = (int64_t)block * kPrepThreads + threadIdx.x; i < a.n_rays; i += (int64_t)a.n_wmax * kPrepThreads)
+        m = max(m, __float_as_uint(fabsf(a.weights[i])));
+    for (int off = kWave / 2; off > 0; off >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, off));
+    if ((threadIdx.x & (kWave - 1)) == 0) wave_max[threadIdx.x / kWave] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < kPrepThreads / kWave; ++k) m = max(m, wave_max[k]);
+        a.wmax_bits[block] = m;
+    }
+}
+
+__device__ inline void table_block(const SynthArgs& a, int block) {
+    if (block < a.n_wmax) wmax_block(a, block);
+    else deconv_block(a, block - a.n_wmax);
+}
+
+// Once per call: every hit resolved, then the tables (blocks hit_blocks and up).
+__global__ __launch_bounds__(kPrepThreads) void prep_kernel(SynthArgs a, int hit_blocks) {
+    if ((int)blockIdx.x >= hit_blocks) {
+        table_block(a, (int)blockIdx.x - hit_blocks);
+        return;
+    }
+    const int64_t k = (int64_t)blockIdx.x * kPrepThreads + threadIdx.x;
+    if (k >= a.n_hits) return;
+    a.hit_rec[k] = resolve_hit(a, k);
     a.hit_rec_v[k] = a.hit_v[k];
 }
 
@@ -210,10 +268,21 @@ __device__ inline void rec_point(const int4 r, float hv, const double* __restric
 // for one chain per hit.  The pair loop of the synthesis then only adds the
 // two antenna legs.  A ray with no usable path (no hits, or out-of-range meta
 // data) stores an inner length of -1.
+//
+// INLINE: small calls, where a launch costs more than resolving each hit once
+// per chirp: the hits are resolved here, and the blocks past the rays' (of the
+// first chirp) compute the call's tables.
 constexpr int kHitRun = 4;
 
-__global__ void geometry_kernel(SynthArgs a) {
-    const int ray = blockIdx.x * blockDim.x + threadIdx.x;
+template <bool INLINE>
+__global__ __launch_bounds__(kPrepThreads) void geometry_kernel(SynthArgs a, int ray_blocks) {
+    if constexpr (INLINE) {
+        if ((int)blockIdx.x >= ray_blocks) {
+            if (blockIdx.y == 0) table_block(a, (int)blockIdx.x - ray_blocks);
+            return;
+        }
+    }
+    const int ray = blockIdx.x * kPrepThreads + threadIdx.x;
     const int jj = blockIdx.y;
     if (ray >= a.n_rays) return;
     const int64_t plane = (int64_t)a.chirp_count * a.n_rays;
@@ -231,8 +300,13 @@ __global__ void geometry_kernel(SynthArgs a) {
                 r[c] = make_int4(0, 0, 0, 0);
                 hv[c] = 0.0f;
                 if (k0 + c < e) {
-                    r[c] = a.hit_rec[k0 + c];
-                    hv[c] = a.hit_rec_v[k0 + c];
+                    if constexpr (INLINE) {
+                        r[c] = resolve_hit(a, k0 + c);
+                        hv[c] = a.hit_v[k0 + c];
+                    } else {
+                        r[c] = a.hit_rec[k0 + c];
+                        hv[c] = a.hit_rec_v[k0 + c];
+                    }
                 }
             }
 #pragma unroll
@@ -544,8 +618,11 @@ __global__ __launch_bounds__(kThreads) void spread_kernel(SynthArgs a) {
     const int P = M + kTaps;
     const int CS = 2 * P + 1;
     for (int i = threadIdx.x; i < kGridCopies * CS; i += kThreads) gq[i] = 0ull;
+    // max|w| = m 2^e2, m in [1/2, 1), from the partial maxima (1 without weights)
+    unsigned wbits = a.n_wmax ? (lane < a.n_wmax ? a.wmax_bits[lane] : 0u) : 0x3f800000u;
+    for (int off = kWave / 2; off > 0; off >>= 1) wbits = max(wbits, (unsigned)__shfl_xor((int)wbits, off));
     int e2;
-    frexpf(__uint_as_float(*a.wmax_bits), &e2);     // max|w| = m 2^e2, m in [1/2, 1)
+    frexpf(__uint_as_float(wbits), &e2);
     const int qexp = 30 - e2;                       // 2^qexp max|w| in [2^29, 2^30)
     __syncthreads();
 
@@ -616,46 +693,6 @@ __global__ __launch_bounds__(kThreads) void spread_kernel(SynthArgs a) {
         }
         out[i] = make_float2((float)ldexp((double)re, -qexp), (float)ldexp((double)im, -qexp));
     }
-}
-
-// *bits = the float bits of max_i |w_i| (nonnegative floats order like their
-// bit patterns); *bits must be zero on entry.  256 threads per block; one
-// atomic per block.
-__global__ __launch_bounds__(256) void wmax_kernel(const float* __restrict__ w, int n, unsigned* bits) {
-    __shared__ unsigned wave_max[256 / kWave];
-    unsigned m = 0u;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        m = max(m, __float_as_uint(fabsf(w[i])));
-    for (int off = kWave / 2; off > 0; off >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, off));
-    if ((threadIdx.x & (kWave - 1)) == 0) wave_max[threadIdx.x / kWave] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < 256 / kWave; ++k) m = max(m, wave_max[k]);
-        atomicMax(bits, m);
-    }
-}
-
-__global__ void set_u32_kernel(unsigned* p, unsigned v) { *p = v; }
-
-// deconv[n] = 1 / psi_hat((n - center) / M), psi_hat(xi) the integral of
-// psi(u) cos(2 pi xi u) over the kernel's support |u| <= kTaps / 2 (psi is
-// even), by the trapezoid rule with kQuad intervals in FP64 (psi falls to
-// e^{-beta} at the ends of its support, where the rule's error vanishes with
-// it).  One wave per n; the lanes' partial sums are combined in a fixed order.
-__global__ __launch_bounds__(kWave) void deconv_kernel(double* deconv, int n_samples, int center, int grid_log2) {
-    const int n = blockIdx.x;
-    const int lane = threadIdx.x;
-    const double xi = (double)(n - center) / (double)(1 << grid_log2);
-    const double h = (double)kTaps / kQuad;
-    double acc = 0.0;
-    for (int i = lane; i <= kQuad; i += kWave) {
-        const double u = -0.5 * kTaps + i * h;
-        const double z = 2.0 * u / kTaps;
-        const double psi = exp(kBeta * (sqrt(fmax(0.0, 1.0 - z * z)) - 1.0));
-        acc += ((i == 0 || i == kQuad) ? 0.5 * h : h) * psi * cospi(2.0 * xi * u);
-    }
-    for (int off = kWave / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    if (lane == 0 && n < n_samples) deconv[n] = 1.0 / acc;
 }
 
 // Workgroup (pair q, batch chirp j): the partitions' grids of the block summed
@@ -981,7 +1018,7 @@ Plan plan(int n_rays, int64_t n_hits, int n_pairs, int chirp_count, int n_sample
     p.rec_bytes = round256(n_hits * (int64_t)sizeof(int4)) + round256(n_hits * (int64_t)sizeof(float));
     p.partial_bytes = (int64_t)p.parts * blocks * n_samples * (int64_t)sizeof(float2);
     p.grid_bytes = round256((int64_t)p.parts * blocks * (int64_t(1) << p.grid_log2) * (int64_t)sizeof(float2));
-    p.deconv_bytes = round256((int64_t)n_samples * (int64_t)sizeof(double)) + 256;   // + the max-weight word
+    p.deconv_bytes = round256((int64_t)n_samples * (int64_t)sizeof(double)) + 256;   // + the largest weights' words
     p.geo_sets = chirp_count > p.batch ? 2 : 1;
     p.total_bytes = p.geo_sets * p.geo_bytes + p.rec_bytes + std::max(p.partial_bytes, p.grid_bytes + p.deconv_bytes);
     return p;
@@ -1197,9 +1234,29 @@ rmd_status helper_stream(hipStream_t* out) {
 // synthesis that last read its set, and each synthesis after its geometry, so
 // the helper stream's work is joined back into `stream` (also under graph
 // capture).  The results are those of the serial order.
+//
+// Before them the call's hits are resolved and, where n_tables > 0, its tables
+// computed: by prep_kernel, or in a call of one small batch (kInlineWork
+// rays x chirps) by the geometry kernel itself.  A ray then resolves its hits
+// once per chirp, which costs less than the launch up to about that size: us
+// per call, own launch and inline, 5003 rays x 8 chirps 22.5 / 21.1,
+// 5003 x 4 20.7 / 18.3, 100000 x 8 59.8 / 62.2, 300000 x 8 133 / 143.  (Before
+// prep_kernel, five launches: 28.6, 27.0, 69.6 and 146.)
+constexpr int64_t kInlineWork = int64_t(1) << 18;
+
 template <class Work>
 rmd_status run_batches(const Plan& p, rmd::SynthArgs a, int32_t chirp0, int32_t chirp_count, int n_rays,
-                       hipStream_t stream, Work&& work) {
+                       int n_tables, hipStream_t stream, Work&& work) {
+    const int ray_blocks = (n_rays + rmd::kPrepThreads - 1) / rmd::kPrepThreads;
+    const bool inline_prep = chirp_count <= p.batch && (int64_t)n_rays * chirp_count <= kInlineWork;
+    if (!inline_prep) {
+        const int hit_blocks = (int)((a.n_hits + rmd::kPrepThreads - 1) / rmd::kPrepThreads);
+        if (hit_blocks + n_tables > 0)
+            hipLaunchKernelGGL(rmd::prep_kernel, dim3((unsigned)(hit_blocks + n_tables)), dim3(rmd::kPrepThreads), 0,
+                               stream, a, hit_blocks);
+        hipError_t e0 = hipGetLastError();
+        if (e0 != hipSuccess) return hip_fail(e0, "prep_kernel launch");
+    }
     char* geo0 = reinterpret_cast<char*>(a.geo);
     auto geometry = [&](int b, hipStream_t st) {
         rmd::SynthArgs g = a;
@@ -1207,7 +1264,12 @@ rmd_status run_batches(const Plan& p, rmd::SynthArgs a, int32_t chirp0, int32_t 
         g.chirp0 = chirp0 + c0;
         g.chirp_count = std::min(p.batch, chirp_count - c0);
         g.geo = reinterpret_cast<double*>(geo0 + (size_t)(b % p.geo_sets) * p.geo_bytes);
-        hipLaunchKernelGGL(rmd::geometry_kernel, dim3((n_rays + 255) / 256, g.chirp_count), dim3(256), 0, st, g);
+        if (inline_prep)
+            hipLaunchKernelGGL(rmd::geometry_kernel<true>, dim3(ray_blocks + n_tables, g.chirp_count),
+                               dim3(rmd::kPrepThreads), 0, st, g, ray_blocks);
+        else
+            hipLaunchKernelGGL(rmd::geometry_kernel<false>, dim3(ray_blocks, g.chirp_count), dim3(rmd::kPrepThreads), 0,
+                               st, g, ray_blocks);
     };
     auto batch_args = [&](int b) {
         rmd::SynthArgs w = a;
@@ -1290,15 +1352,6 @@ void launch_fft(const float2* in, float2* out, int logl, int lines, int lg, hipS
     else if constexpr ((1 << LOGL) < RMD_MAX_FFT) launch_fft<STRIDED, LOGL + 1>(in, out, logl, lines, lg, stream);
 }
 
-// Resolves the hits into a.hit_rec once per call (both methods).
-rmd_status resolve_hits(const rmd::SynthArgs& a, hipStream_t stream) {
-    if (a.n_hits > 0)
-        hipLaunchKernelGGL(rmd::resolve_kernel, dim3((unsigned)((a.n_hits + 255) / 256)), dim3(256), 0, stream, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "resolve_kernel launch");
-    return RMD_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -1311,34 +1364,23 @@ rmd_status rmd_if_cube(const rmd_scene* scene, const rmd_radar* radar, int32_t n
     rmd_status st = cube_setup(scene, radar, n_pairs, pairs, weights, chirp0, chirp_count, s, workspace,
                                workspace_bytes, p, a);
     if (st != RMD_OK) return st;
-    st = resolve_hits(a, stream);
-    if (st != RMD_OK) return st;
     const int M = 1 << p.grid_log2;
     a.grid_log2 = p.grid_log2;
     a.center = radar->n_samples / 2;
     char* tail = static_cast<char*>(workspace) + p.geo_sets * p.geo_bytes + p.rec_bytes + p.grid_bytes;
-    auto* wmax = reinterpret_cast<unsigned*>(tail);
-    auto* deconv = reinterpret_cast<double*>(tail + 256);
-    a.deconv = deconv;
-    a.wmax_bits = wmax;
+    a.wmax_bits = reinterpret_cast<unsigned*>(tail);           // 256 bytes
+    a.deconv = reinterpret_cast<double*>(tail + 256);
+    a.n_wmax = weights ? (int)std::min<int64_t>(rmd::kWave, (scene->n_rays + 2047) / 2048) : 0;
     std::memcpy(a.tap_even, tap_poly().even, sizeof(a.tap_even));
     std::memcpy(a.tap_odd, tap_poly().odd, sizeof(a.tap_odd));
-    hipLaunchKernelGGL(rmd::deconv_kernel, dim3(radar->n_samples), dim3(rmd::kWave), 0, stream, deconv,
-                       radar->n_samples, a.center, a.grid_log2);
-    if (weights) {
-        hipLaunchKernelGGL(rmd::set_u32_kernel, dim3(1), dim3(1), 0, stream, wmax, 0u);
-        const int blocks = (int)std::min<int64_t>(1024, (scene->n_rays + 255) / 256);
-        hipLaunchKernelGGL(rmd::wmax_kernel, dim3(blocks), dim3(256), 0, stream, weights, scene->n_rays, wmax);
-    } else {
-        hipLaunchKernelGGL(rmd::set_u32_kernel, dim3(1), dim3(1), 0, stream, wmax, 0x3f800000u);   // 1.0f
-    }
+    const int n_tables = a.n_wmax + (radar->n_samples + rmd::kPrepThreads / rmd::kWave - 1) / (rmd::kPrepThreads / rmd::kWave);
     const size_t spread_lds =
         (size_t)rmd::kGridCopies * (2 * (M + rmd::kTaps) + 1) * sizeof(unsigned long long);
     const size_t finish_lds = (size_t)(M / 2 + M) * sizeof(double2);
     // Chirp batches: the spreading and the transform of each batch after its
     // geometry (the partition count is the same for every batch: a shorter
     // last batch uses part of the buffers).
-    return run_batches(p, a, chirp0, chirp_count, scene->n_rays, stream,
+    return run_batches(p, a, chirp0, chirp_count, scene->n_rays, n_tables, stream,
                        [&](const rmd::SynthArgs& w, int nb, int c0) {
                            const dim3 grid((unsigned)((int64_t)n_pairs * nb * p.parts));
                            hipLaunchKernelGGL(rmd::spread_kernel, grid, dim3(rmd::kThreads), spread_lds, stream, w);
@@ -1373,12 +1415,10 @@ rmd_status rmd_if_cube_direct(const rmd_scene* scene, const rmd_radar* radar, in
     rmd_status st = cube_setup(scene, radar, n_pairs, pairs, weights, chirp0, chirp_count, s, workspace,
                                workspace_bytes, p, a);
     if (st != RMD_OK) return st;
-    st = resolve_hits(a, stream);
-    if (st != RMD_OK) return st;
     // Chirp batches: the synthesis and the partition sums of each batch after
     // its geometry.
     const int n_samples = radar->n_samples;
-    return run_batches(p, a, chirp0, chirp_count, scene->n_rays, stream,
+    return run_batches(p, a, chirp0, chirp_count, scene->n_rays, 0, stream,
                        [&](const rmd::SynthArgs& w, int nb, int c0) {
                            const dim3 grid((unsigned)((int64_t)n_pairs * w.n_passes * nb * p.parts));
                            hipLaunchKernelGGL(rmd::synth_kernel, grid, dim3(rmd::kThreads), 0, stream, w);
