@@ -87,7 +87,6 @@ constexpr int kTapDeg = 8;
 static_assert(kTapDeg % 2 == 0 && kTaps % 2 == 0, "taps come in mirrored pairs; even degree");
 constexpr double kBeta = 2.30 * kTaps;
 constexpr int kMinGridLog2 = 6;          // M >= 64
-constexpr int kGridCopies = 2;           // spreading grids per workgroup (lanes split by parity)
 constexpr int kQuad = 256;               // trapezoid intervals of the psi_hat quadrature
 
 struct SynthArgs {
@@ -586,6 +585,16 @@ __global__ __launch_bounds__(kThreads) void synth_kernel(SynthArgs a) {
 // does not depend on scheduling (LDS float atomics would not be, and on this
 // chip they are several times slower than integer ones).
 //
+// What bounds it is the LDS: 16 atomics a ray, whose lanes meet in its banks.
+// With two copies of the grid side by side, one for even and one for odd lanes,
+// an atomic of 64 lanes took 13 cycles against 4 without conflicts, and the LDS
+// was active 81 % of the time (vector instructions 71 %).  COPIES interleaved
+// copies, lane l adding into copy l % COPIES of each cell, give each copy 32 /
+// COPIES bank pairs of its own: fewer lanes can meet, on a cell or on a bank.
+// us per call before / after, 12 pairs and 16 chirps: 2^20 rays, M = 1024
+// 1901 / 1664; 400000 rays, M = 1024 828 / 718, 512 1002 / 662, 256 1194 / 656,
+// 64 1172 / 594.  The sums are exact, so neither COPIES nor THREADS changes a bit.
+//
 // Each wave takes the partition's rays 64 at a time, one ray per lane (the
 // same super-group order and geometry prefetch as synth_kernel): the lane forms
 // the ray's phases in FP64, its grid position x = M theta, the first cell
@@ -594,7 +603,8 @@ __global__ __launch_bounds__(kThreads) void synth_kernel(SynthArgs a) {
 // values by Horner's rule and adds the contributions into cells l0 .. l0 +
 // kTaps - 1 (modulo M).  At the end the grid is scaled back and written as
 // the partition's float32 grid.
-__global__ __launch_bounds__(kThreads) void spread_kernel(SynthArgs a) {
+template <int COPIES, int THREADS>
+__global__ __launch_bounds__(THREADS) void spread_kernel(SynthArgs a) {
     extern __shared__ unsigned long long gq[];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -611,13 +621,10 @@ __global__ __launch_bounds__(kThreads) void spread_kernel(SynthArgs a) {
     // Each plane has kTaps cells of padding: padded cell i holds grid cell
     // (i - kTaps / 2) mod M, so a ray's taps are one address plus constant
     // offsets; the wrapped cells are folded back when the grid is written.
-    // Even and odd lanes add into separate copies of the grid (2P + 1 cells
-    // apart, so equal cells of the two copies sit in different banks): rays
-    // of one target share cells, and two copies halve the lanes of one
-    // atomic instruction that can meet on the same address.
+    // Lane l adds into copy l % COPIES of the grid; the copies of a cell are
+    // neighbours, so each copy has 32 / COPIES of the bank pairs to itself.
     const int P = M + kTaps;
-    const int CS = 2 * P + 1;
-    for (int i = threadIdx.x; i < kGridCopies * CS; i += kThreads) gq[i] = 0ull;
+    for (int i = threadIdx.x; i < COPIES * 2 * P; i += THREADS) gq[i] = 0ull;
     // max|w| = m 2^e2, m in [1/2, 1), from the partial maxima (1 without weights)
     unsigned wbits = a.n_wmax ? (lane < a.n_wmax ? a.wmax_bits[lane] : 0u) : 0x3f800000u;
     for (int off = kWave / 2; off > 0; off >>= 1) wbits = max(wbits, (unsigned)__shfl_xor((int)wbits, off));
@@ -630,9 +637,9 @@ __global__ __launch_bounds__(kThreads) void spread_kernel(SynthArgs a) {
     const int r1 = min(a.n_rays, r0 + a.rays_per_part);
     const double fM = (double)M;
     Geo gn = load_geo(a, r0 + wave * kWave + lane, r1, jj);
-    for (int sbase = r0 + wave * kWave; sbase < r1; sbase += kThreads) {
+    for (int sbase = r0 + wave * kWave; sbase < r1; sbase += THREADS) {
         const Phases own = ray_phases(a, gn, pq);
-        gn = load_geo(a, sbase + kThreads + lane, r1, jj);      // next super-group, in flight meanwhile
+        gn = load_geo(a, sbase + THREADS + lane, r1, jj);      // next super-group, in flight meanwhile
         if (own.w != 0.0f) {
             const double x = own.theta * fM;                   // grid position in [0, M)
             const double l0 = ceil(x - 0.5 * kTaps);
@@ -660,35 +667,35 @@ __global__ __launch_bounds__(kThreads) void spread_kernel(SynthArgs a) {
             // [0, 1) (the clamp only guards non-finite pair coordinates), so
             // the taps' padded cells l0 + kTaps / 2 + t lie in [0, M + kTaps).
             const int base = min(max((int)l0, -kTaps / 2), M - kTaps / 2);
-            unsigned long long* cr = gq + (lane & (kGridCopies - 1)) * CS + (base + kTaps / 2);
-            unsigned long long* ci = cr + P;
+            unsigned long long* cr = gq + (base + kTaps / 2) * COPIES + (lane & (COPIES - 1));
+            unsigned long long* ci = cr + P * COPIES;
 #pragma unroll
             for (int t = 0; t < kTaps; ++t) {
                 // |k c| < 2^31 by the choice of qexp; conversion rounds toward zero
                 const long long vr = (int)(k[t] * c.x);
                 const long long vi = (int)(k[t] * c.y);
-                atomicAdd(cr + t, (unsigned long long)vr);
-                atomicAdd(ci + t, (unsigned long long)vi);
+                atomicAdd(cr + t * COPIES, (unsigned long long)vr);
+                atomicAdd(ci + t * COPIES, (unsigned long long)vi);
             }
         }
     }
     __syncthreads();
     float2* out = a.partial + (((int64_t)part * a.n_pairs + q) * a.chirp_count + jj) * (int64_t)M;
-    for (int i = threadIdx.x; i < M; i += kThreads) {
+    for (int i = threadIdx.x; i < M; i += THREADS) {
         const int h = i + kTaps / 2;                        // padded cell of grid cell i
         long long re = 0, im = 0;
 #pragma unroll
-        for (int cp = 0; cp < kGridCopies; ++cp) {
-            const unsigned long long* g0 = gq + cp * CS;
-            re += (long long)g0[h];
-            im += (long long)g0[P + h];
+        for (int cp = 0; cp < COPIES; ++cp) {
+            const unsigned long long* g0 = gq + cp;
+            re += (long long)g0[h * COPIES];
+            im += (long long)g0[(P + h) * COPIES];
             if (i < kTaps / 2) {                            // wrapped past the end
-                re += (long long)g0[h + M];
-                im += (long long)g0[P + h + M];
+                re += (long long)g0[(h + M) * COPIES];
+                im += (long long)g0[(P + h + M) * COPIES];
             }
             if (i >= M - kTaps / 2) {                       // wrapped below the start
-                re += (long long)g0[h - M];
-                im += (long long)g0[P + h - M];
+                re += (long long)g0[(h - M) * COPIES];
+                im += (long long)g0[(P + h - M) * COPIES];
             }
         }
         out[i] = make_float2((float)ldexp((double)re, -qexp), (float)ldexp((double)im, -qexp));
@@ -1352,6 +1359,38 @@ void launch_fft(const float2* in, float2* out, int logl, int lines, int lg, hipS
     else if constexpr ((1 << LOGL) < RMD_MAX_FFT) launch_fft<STRIDED, LOGL + 1>(in, out, logl, lines, lg, stream);
 }
 
+template <int COPIES, int THREADS>
+void launch_spread_as(const rmd::SynthArgs& a, dim3 grid, int M, hipStream_t stream) {
+    const size_t lds = (size_t)COPIES * 2 * (M + rmd::kTaps) * sizeof(unsigned long long);
+    hipLaunchKernelGGL((rmd::spread_kernel<COPIES, THREADS>), grid, dim3(THREADS), lds, stream, a);
+}
+
+template <int THREADS>
+void launch_spread_copies(const rmd::SynthArgs& a, dim3 grid, int M, int copies, hipStream_t stream) {
+    if (copies >= 16) launch_spread_as<16, THREADS>(a, grid, M, stream);
+    else if (copies == 8) launch_spread_as<8, THREADS>(a, grid, M, stream);
+    else if (copies == 4) launch_spread_as<4, THREADS>(a, grid, M, stream);
+    else launch_spread_as<2, THREADS>(a, grid, M, stream);
+}
+
+// Grid copies and threads of a spreading workgroup.  Copies spread the atomics
+// over the banks but are cleared and summed once per workgroup: about 2048
+// cells of them, and 4096 (with 512 threads, for the same LDS per wave) where a
+// partition is long enough to pay for it.  512 threads also where a workgroup a
+// CU or less is all there is, and where two copies of the largest grid leave
+// room for two workgroups only.  us per call with 2048 cells / with 4096, 12
+// pairs and 16 chirps, by M and rays per partition: 1024: 2560 rays 247 / 244,
+// 4352 400 / 377, 6144 550 / 510; 512: 3072 280 / 287, 4352 366 / 356, 6144
+// 513 / 475; 256: 4352 333 / 354, 6144 456 / 453, 9472 655 / 656; 128: 9472
+// 615 / 603.  256 threads / 512: 8 and 16 workgroups a CU of M = 1024 147.5 /
+// 154.7, one a CU 22.4 / 20.9; M = 2048 176 / 167.
+void launch_spread(const rmd::SynthArgs& a, dim3 grid, int M, int rays_per_part, hipStream_t stream) {
+    const bool long_part = rays_per_part >= (M >= 512 ? 4096 : 8192);
+    const int copies = std::min(16, std::max(2, (long_part ? 4096 : 2048) / M));
+    if (long_part || M >= 2048 || grid.x <= 256) launch_spread_copies<512>(a, grid, M, copies, stream);
+    else launch_spread_copies<256>(a, grid, M, copies, stream);
+}
+
 }  // namespace
 
 extern "C" {
@@ -1374,8 +1413,6 @@ rmd_status rmd_if_cube(const rmd_scene* scene, const rmd_radar* radar, int32_t n
     std::memcpy(a.tap_even, tap_poly().even, sizeof(a.tap_even));
     std::memcpy(a.tap_odd, tap_poly().odd, sizeof(a.tap_odd));
     const int n_tables = a.n_wmax + (radar->n_samples + rmd::kPrepThreads / rmd::kWave - 1) / (rmd::kPrepThreads / rmd::kWave);
-    const size_t spread_lds =
-        (size_t)rmd::kGridCopies * (2 * (M + rmd::kTaps) + 1) * sizeof(unsigned long long);
     const size_t finish_lds = (size_t)(M / 2 + M) * sizeof(double2);
     // Chirp batches: the spreading and the transform of each batch after its
     // geometry (the partition count is the same for every batch: a shorter
@@ -1383,7 +1420,7 @@ rmd_status rmd_if_cube(const rmd_scene* scene, const rmd_radar* radar, int32_t n
     return run_batches(p, a, chirp0, chirp_count, scene->n_rays, n_tables, stream,
                        [&](const rmd::SynthArgs& w, int nb, int c0) {
                            const dim3 grid((unsigned)((int64_t)n_pairs * nb * p.parts));
-                           hipLaunchKernelGGL(rmd::spread_kernel, grid, dim3(rmd::kThreads), spread_lds, stream, w);
+                           launch_spread(w, grid, M, p.rays_per_part, stream);
                            hipLaunchKernelGGL(rmd::finish_kernel, dim3((unsigned)(n_pairs * nb)),
                                               dim3(rmd::kFinishThreads), finish_lds, stream, w,
                                               reinterpret_cast<float2*>(s), chirp_count, c0);
