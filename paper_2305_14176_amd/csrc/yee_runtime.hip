@@ -200,13 +200,13 @@ void layout(yee_ctx* c) {
   take(c->coef, (size_t)c->nsx * c->nsy * c->nsz * 2 * c->csize);
   c->prof_len = std::max({d.nx, d.ny, d.nz}) + 1;
   take(c->prof, 2 * 3 * 3 * c->prof_len * c->csize);
-  take(c->prof4, 2 * 3 * 4 * c->prof_len * c->csize);
   take(c->pecplane, (size_t)d.nz * 4);
   take(c->pecmask, c->pec_k.size() * (size_t)d.ny * c->px);
   take(c->rowflag, (size_t)d.nz * d.ny);
   take(c->srcr, c->src.size() * sizeof(yee::SrcDev));
   take(c->prober, np * sizeof(int4));
   take(c->freqr, nf * sizeof(double));
+  take(c->prof4, 2 * 3 * 4 * c->prof_len * c->csize);
   c->ws_bytes = (int64_t)off;
 }
 
