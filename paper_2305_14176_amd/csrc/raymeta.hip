@@ -287,20 +287,23 @@ __device__ inline void rec_point(const int4 r, float hv, const double* __restric
 // data) stores an inner length of -1.
 //
 // INLINE: small calls, where a launch costs more than resolving each hit once
-// per chirp: the hits are resolved here, and the blocks past the rays' (of the
-// first chirp) compute the call's tables.
+// per chirp: the hits are resolved here, and the first n_tables blocks compute
+// the call's tables (first, as they take the longest; the grid is
+// one-dimensional, chirps slowest, so that they come once).
 constexpr int kHitRun = 4;
 
 template <bool INLINE>
-__global__ __launch_bounds__(kPrepThreads) void geometry_kernel(SynthArgs a, int ray_blocks) {
+__global__ __launch_bounds__(kPrepThreads) void geometry_kernel(SynthArgs a, int ray_blocks, int n_tables) {
+    int block = blockIdx.x, jj = blockIdx.y;
     if constexpr (INLINE) {
-        if ((int)blockIdx.x >= ray_blocks) {
-            if (blockIdx.y == 0) table_block(a, (int)blockIdx.x - ray_blocks);
+        if (block < n_tables) {
+            table_block(a, block);
             return;
         }
+        jj = (block - n_tables) / ray_blocks;
+        block = (block - n_tables) % ray_blocks;
     }
-    const int ray = blockIdx.x * kPrepThreads + threadIdx.x;
-    const int jj = blockIdx.y;
+    const int ray = block * kPrepThreads + threadIdx.x;
     if (ray >= a.n_rays) return;
     const int64_t plane = (int64_t)a.chirp_count * a.n_rays;
     double* g = a.geo + (int64_t)jj * a.n_rays + ray;
@@ -1305,11 +1308,11 @@ rmd_status run_batches(const Plan& p, rmd::SynthArgs a, int32_t chirp0, int32_t 
         g.chirp_count = std::min(p.batch, chirp_count - c0);
         g.geo = reinterpret_cast<double*>(geo0 + (size_t)(b % p.geo_sets) * p.geo_bytes);
         if (inline_prep)
-            hipLaunchKernelGGL(rmd::geometry_kernel<true>, dim3(ray_blocks + n_tables, g.chirp_count),
-                               dim3(rmd::kPrepThreads), 0, st, g, ray_blocks);
+            hipLaunchKernelGGL(rmd::geometry_kernel<true>, dim3((unsigned)(n_tables + ray_blocks * g.chirp_count)),
+                               dim3(rmd::kPrepThreads), 0, st, g, ray_blocks, n_tables);
         else
             hipLaunchKernelGGL(rmd::geometry_kernel<false>, dim3(ray_blocks, g.chirp_count), dim3(rmd::kPrepThreads), 0,
-                               st, g, ray_blocks);
+                               st, g, ray_blocks, 0);
     };
     auto batch_args = [&](int b) {
         rmd::SynthArgs w = a;
