@@ -14,9 +14,9 @@
 // row below to each row.  The price is about 1.6 times the arithmetic and
 // twice the cache reads per cell, which a small grid has room for.
 //
-// Measured per step against the march (us): 32^3 FP64 without CPML 8.7 -> 5.1,
-// 12 x 12 x 140 FP32 8.7 -> 5.2, 32^3 FP32 with CPML 8 11.2 -> 5.5, 64^3 FP32
-// 12.4 -> 8.2, 96^3 22.7 -> 26.4 (direct_rule below draws the line).
+// Measured per step against the march (us): 32^3 FP64 without CPML 8.8 -> 4.0,
+// 12 x 12 x 140 FP32 8.5 -> 4.1, 32^3 FP32 with CPML 8 11.1 -> 4.0, 64^3 FP32
+// 12.3 -> 8.0, 96^3 22.7 -> 26.4 (direct_rows in yee_runtime.hip draws the line).
 #pragma once
 
 #include "yee_kernels.hpp"
