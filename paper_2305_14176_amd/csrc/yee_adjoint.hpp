@@ -48,7 +48,7 @@ struct AdjArgs {
   const C* pin;             // psi adjoint (E side in adj_h, H side in adj_e), old
   C* pout;                  // new
   uint32_t psoff[6];        // element offset of the pair array holding each auxiliary (see yee_kernels.hpp)
-  const C* prof;            // CPML profiles [side E,H][axis][1 - b | a | 1/kappa][plen]
+  const C* prof;            // CPML profiles [side E,H][axis][plen][1 - b, a, 1/kappa]
   int32_t plen;
   const int32_t* seg;       // block index per cell: x [px] | y [ny] | z [nz]
   const Coef2<C>* coef;     // (Ca, Cb) per block
@@ -155,17 +155,21 @@ adj_h_kernel(const AdjArgs<C, C> a) {
   const C* pr = a.prof;
   const int pl = a.plen;
 
+  // (The profile loads come first in each layer: left to the scheduler they are
+  // issued after a wait for the auxiliaries, 26.4 instead of 24.9 us at 128^3 FP32.)
   // dbar of the y terms (XY: +Ex, ZY: -Ez) at E samples j and j + 1
   C dxy0 = ux, dxy1 = ux_y, dzy0 = -uz, dzy1 = -uz_y;
   if (in_layer(j, ny, Ly)) {
     const uint32_t q = ((uint32_t)k * (2 * Ly) + slab(j, ny, Ly)) * px + i;
-    const C kv = pr[5 * pl + j], av = pr[4 * pl + j];
+    const C kv = pr[3 * (pl + j) + 2], av = pr[3 * (pl + j) + 1];
+    __builtin_amdgcn_sched_barrier(0);
     dxy0 = kv * ux + av * (P[a.psoff[PEXY] + 2 * q + psi_member(PEXY)] + ux);
     dzy0 = -kv * uz + av * (P[a.psoff[PEZY] + 2 * q + psi_member(PEZY)] - uz);
   }
   if (yp && in_layer(j + 1, ny, Ly)) {
     const uint32_t q = ((uint32_t)k * (2 * Ly) + slab(j + 1, ny, Ly)) * px + i;
-    const C kv = pr[5 * pl + j + 1], av = pr[4 * pl + j + 1];
+    const C kv = pr[3 * (pl + j + 1) + 2], av = pr[3 * (pl + j + 1) + 1];
+    __builtin_amdgcn_sched_barrier(0);
     dxy1 = kv * ux_y + av * (P[a.psoff[PEXY] + 2 * q + psi_member(PEXY)] + ux_y);
     dzy1 = -kv * uz_y + av * (P[a.psoff[PEZY] + 2 * q + psi_member(PEZY)] - uz_y);
   }
@@ -173,13 +177,15 @@ adj_h_kernel(const AdjArgs<C, C> a) {
   C dyz0 = uy, dyz1 = uy_z, dxz0 = -ux, dxz1 = -ux_z;
   if (in_layer(k, nz, Lz)) {
     const uint32_t q = ((uint32_t)slab(k, nz, Lz) * ny + j) * px + i;
-    const C kv = pr[8 * pl + k], av = pr[7 * pl + k];
+    const C kv = pr[3 * (2 * pl + k) + 2], av = pr[3 * (2 * pl + k) + 1];
+    __builtin_amdgcn_sched_barrier(0);
     dyz0 = kv * uy + av * (P[a.psoff[PEYZ] + 2 * q + psi_member(PEYZ)] + uy);
     dxz0 = -kv * ux + av * (P[a.psoff[PEXZ] + 2 * q + psi_member(PEXZ)] - ux);
   }
   if (zp && in_layer(k + 1, nz, Lz)) {
     const uint32_t q = ((uint32_t)slab(k + 1, nz, Lz) * ny + j) * px + i;
-    const C kv = pr[8 * pl + k + 1], av = pr[7 * pl + k + 1];
+    const C kv = pr[3 * (2 * pl + k + 1) + 2], av = pr[3 * (2 * pl + k + 1) + 1];
+    __builtin_amdgcn_sched_barrier(0);
     dyz1 = kv * uy_z + av * (P[a.psoff[PEYZ] + 2 * q + psi_member(PEYZ)] + uy_z);
     dxz1 = -kv * ux_z + av * (P[a.psoff[PEXZ] + 2 * q + psi_member(PEXZ)] - ux_z);
   }
@@ -188,13 +194,15 @@ adj_h_kernel(const AdjArgs<C, C> a) {
   const uint32_t qx = ((uint32_t)k * ny + j) * (2 * Lx);
   if (in_layer(i, nx, Lx)) {
     const uint32_t q = qx + slab(i, nx, Lx);
-    const C kv = pr[2 * pl + i], av = pr[1 * pl + i];
+    const C kv = pr[3 * i + 2], av = pr[3 * i + 1];
+    __builtin_amdgcn_sched_barrier(0);
     dzx0 = kv * uz + av * (P[a.psoff[PEZX] + 2 * q + psi_member(PEZX)] + uz);
     dyx0 = -kv * uy + av * (P[a.psoff[PEYX] + 2 * q + psi_member(PEYX)] - uy);
   }
   if (xp && in_layer(i + 1, nx, Lx)) {
     const uint32_t q = qx + slab(i + 1, nx, Lx);
-    const C kv = pr[2 * pl + i + 1], av = pr[1 * pl + i + 1];
+    const C kv = pr[3 * (i + 1) + 2], av = pr[3 * (i + 1) + 1];
+    __builtin_amdgcn_sched_barrier(0);
     dzx1 = kv * uz_x + av * (P[a.psoff[PEZX] + 2 * q + psi_member(PEZX)] + uz_x);
     dyx1 = -kv * uy_x + av * (P[a.psoff[PEYX] + 2 * q + psi_member(PEYX)] - uy_x);
   }
@@ -212,19 +220,19 @@ adj_h_kernel(const AdjArgs<C, C> a) {
   // psi_E adjoint of the own samples: P <- b (P + s u)
   if (in_layer(j, ny, Ly)) {
     const uint32_t q = ((uint32_t)k * (2 * Ly) + slab(j, ny, Ly)) * px + i;
-    const C ob = pr[3 * pl + j];
+    const C ob = pr[3 * (pl + j)];
     { const C t = P[a.psoff[PEXY] + 2 * q + psi_member(PEXY)] + ux; a.pout[a.psoff[PEXY] + 2 * q + psi_member(PEXY)] = t - ob * t; }
     { const C t = P[a.psoff[PEZY] + 2 * q + psi_member(PEZY)] - uz; a.pout[a.psoff[PEZY] + 2 * q + psi_member(PEZY)] = t - ob * t; }
   }
   if (in_layer(k, nz, Lz)) {
     const uint32_t q = ((uint32_t)slab(k, nz, Lz) * ny + j) * px + i;
-    const C ob = pr[6 * pl + k];
+    const C ob = pr[3 * (2 * pl + k)];
     { const C t = P[a.psoff[PEYZ] + 2 * q + psi_member(PEYZ)] + uy; a.pout[a.psoff[PEYZ] + 2 * q + psi_member(PEYZ)] = t - ob * t; }
     { const C t = P[a.psoff[PEXZ] + 2 * q + psi_member(PEXZ)] - ux; a.pout[a.psoff[PEXZ] + 2 * q + psi_member(PEXZ)] = t - ob * t; }
   }
   if (in_layer(i, nx, Lx)) {
     const uint32_t q = qx + slab(i, nx, Lx);
-    const C ob = pr[0 * pl + i];
+    const C ob = pr[3 * i];
     { const C t = P[a.psoff[PEZX] + 2 * q + psi_member(PEZX)] + uz; a.pout[a.psoff[PEZX] + 2 * q + psi_member(PEZX)] = t - ob * t; }
     { const C t = P[a.psoff[PEYX] + 2 * q + psi_member(PEYX)] - uy; a.pout[a.psoff[PEYX] + 2 * q + psi_member(PEYX)] = t - ob * t; }
   }
@@ -262,13 +270,15 @@ adj_e_kernel(const AdjArgs<T, C> a) {
   C gxy1 = -mu * hx, gxy0 = -mu * hx_y, gzy1 = mu * hz, gzy0 = mu * hz_y;
   if (in_layer(j, ny, Ly)) {
     const uint32_t q = ((uint32_t)k * (2 * Ly) + slab(j, ny, Ly)) * px + i;
-    const C kv = pr[14 * pl + j], av = pr[13 * pl + j];
+    const C kv = pr[3 * (4 * pl + j) + 2], av = pr[3 * (4 * pl + j) + 1];
+    __builtin_amdgcn_sched_barrier(0);
     gxy1 = -mu * kv * hx + av * (Q[a.psoff[PHXY] + 2 * q + psi_member(PHXY)] - mu * hx);
     gzy1 = mu * kv * hz + av * (Q[a.psoff[PHZY] + 2 * q + psi_member(PHZY)] + mu * hz);
   }
   if (ym && in_layer(j - 1, ny, Ly)) {
     const uint32_t q = ((uint32_t)k * (2 * Ly) + slab(j - 1, ny, Ly)) * px + i;
-    const C kv = pr[14 * pl + j - 1], av = pr[13 * pl + j - 1];
+    const C kv = pr[3 * (4 * pl + j - 1) + 2], av = pr[3 * (4 * pl + j - 1) + 1];
+    __builtin_amdgcn_sched_barrier(0);
     gxy0 = -mu * kv * hx_y + av * (Q[a.psoff[PHXY] + 2 * q + psi_member(PHXY)] - mu * hx_y);
     gzy0 = mu * kv * hz_y + av * (Q[a.psoff[PHZY] + 2 * q + psi_member(PHZY)] + mu * hz_y);
   }
@@ -276,13 +286,15 @@ adj_e_kernel(const AdjArgs<T, C> a) {
   C gyz1 = -mu * hy, gyz0 = -mu * hy_z, gxz1 = mu * hx, gxz0 = mu * hx_z;
   if (in_layer(k, nz, Lz)) {
     const uint32_t q = ((uint32_t)slab(k, nz, Lz) * ny + j) * px + i;
-    const C kv = pr[17 * pl + k], av = pr[16 * pl + k];
+    const C kv = pr[3 * (5 * pl + k) + 2], av = pr[3 * (5 * pl + k) + 1];
+    __builtin_amdgcn_sched_barrier(0);
     gyz1 = -mu * kv * hy + av * (Q[a.psoff[PHYZ] + 2 * q + psi_member(PHYZ)] - mu * hy);
     gxz1 = mu * kv * hx + av * (Q[a.psoff[PHXZ] + 2 * q + psi_member(PHXZ)] + mu * hx);
   }
   if (zm && in_layer(k - 1, nz, Lz)) {
     const uint32_t q = ((uint32_t)slab(k - 1, nz, Lz) * ny + j) * px + i;
-    const C kv = pr[17 * pl + k - 1], av = pr[16 * pl + k - 1];
+    const C kv = pr[3 * (5 * pl + k - 1) + 2], av = pr[3 * (5 * pl + k - 1) + 1];
+    __builtin_amdgcn_sched_barrier(0);
     gyz0 = -mu * kv * hy_z + av * (Q[a.psoff[PHYZ] + 2 * q + psi_member(PHYZ)] - mu * hy_z);
     gxz0 = mu * kv * hx_z + av * (Q[a.psoff[PHXZ] + 2 * q + psi_member(PHXZ)] + mu * hx_z);
   }
@@ -291,13 +303,15 @@ adj_e_kernel(const AdjArgs<T, C> a) {
   const uint32_t qx = ((uint32_t)k * ny + j) * (2 * Lx);
   if (in_layer(i, nx, Lx)) {
     const uint32_t q = qx + slab(i, nx, Lx);
-    const C kv = pr[11 * pl + i], av = pr[10 * pl + i];
+    const C kv = pr[3 * (3 * pl + i) + 2], av = pr[3 * (3 * pl + i) + 1];
+    __builtin_amdgcn_sched_barrier(0);
     gzx1 = -mu * kv * hz + av * (Q[a.psoff[PHZX] + 2 * q + psi_member(PHZX)] - mu * hz);
     gyx1 = mu * kv * hy + av * (Q[a.psoff[PHYX] + 2 * q + psi_member(PHYX)] + mu * hy);
   }
   if (xm && in_layer(i - 1, nx, Lx)) {
     const uint32_t q = qx + slab(i - 1, nx, Lx);
-    const C kv = pr[11 * pl + i - 1], av = pr[10 * pl + i - 1];
+    const C kv = pr[3 * (3 * pl + i - 1) + 2], av = pr[3 * (3 * pl + i - 1) + 1];
+    __builtin_amdgcn_sched_barrier(0);
     gzx0 = -mu * kv * hz_x + av * (Q[a.psoff[PHZX] + 2 * q + psi_member(PHZX)] - mu * hz_x);
     gyx0 = mu * kv * hy_x + av * (Q[a.psoff[PHYX] + 2 * q + psi_member(PHYX)] + mu * hy_x);
   }
@@ -355,19 +369,19 @@ adj_e_kernel(const AdjArgs<T, C> a) {
   // psi_H adjoint of the own samples: Q <- b (Q - mu s H_bar)
   if (in_layer(j, ny, Ly)) {
     const uint32_t q = ((uint32_t)k * (2 * Ly) + slab(j, ny, Ly)) * px + i;
-    const C ob = pr[12 * pl + j];
+    const C ob = pr[3 * (4 * pl + j)];
     { const C t = Q[a.psoff[PHXY] + 2 * q + psi_member(PHXY)] - mu * hx; a.pout[a.psoff[PHXY] + 2 * q + psi_member(PHXY)] = t - ob * t; }
     { const C t = Q[a.psoff[PHZY] + 2 * q + psi_member(PHZY)] + mu * hz; a.pout[a.psoff[PHZY] + 2 * q + psi_member(PHZY)] = t - ob * t; }
   }
   if (in_layer(k, nz, Lz)) {
     const uint32_t q = ((uint32_t)slab(k, nz, Lz) * ny + j) * px + i;
-    const C ob = pr[15 * pl + k];
+    const C ob = pr[3 * (5 * pl + k)];
     { const C t = Q[a.psoff[PHYZ] + 2 * q + psi_member(PHYZ)] - mu * hy; a.pout[a.psoff[PHYZ] + 2 * q + psi_member(PHYZ)] = t - ob * t; }
     { const C t = Q[a.psoff[PHXZ] + 2 * q + psi_member(PHXZ)] + mu * hx; a.pout[a.psoff[PHXZ] + 2 * q + psi_member(PHXZ)] = t - ob * t; }
   }
   if (in_layer(i, nx, Lx)) {
     const uint32_t q = qx + slab(i, nx, Lx);
-    const C ob = pr[9 * pl + i];
+    const C ob = pr[3 * (3 * pl + i)];
     { const C t = Q[a.psoff[PHZX] + 2 * q + psi_member(PHZX)] - mu * hz; a.pout[a.psoff[PHZX] + 2 * q + psi_member(PHZX)] = t - ob * t; }
     { const C t = Q[a.psoff[PHYX] + 2 * q + psi_member(PHYX)] + mu * hy; a.pout[a.psoff[PHYX] + 2 * q + psi_member(PHYX)] = t - ob * t; }
   }

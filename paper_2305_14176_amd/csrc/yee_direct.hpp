@@ -33,6 +33,12 @@ __host__ __device__ inline size_t direct_lds_bytes_for(int ty, int wpr, size_t c
          ~size_t(15);
 }
 
+// CPML profile of one sample
+template <class C>
+struct Prof {
+  C omb, a, kinv;   // 1 - b, a, 1/kappa
+};
+
 // lane i gets lane i+1's value (0 into lane 63); lane i-1's (0 into lane 0)
 template <class C, int CTRL>
 __device__ __forceinline__ C lane_shift(C v) {
@@ -161,33 +167,34 @@ __device__ __forceinline__ void direct_tile(const StepArgs<T, C>& a, const int y
   const int pln = a.pec_plane[k];
   // Auxiliaries (H side of planes k and k-1, E side of plane k) and profiles
   // of the layers the wave is in
-  const Prof<C>* pf = a.prof4;
-  const int pl = a.plen;
+  auto profile = [&](int side, int axis, int q) __attribute__((always_inline)) {
+    return reinterpret_cast<const Prof<C>*>(a.prof)[(side * 3 + axis) * a.plen + q];   // one load
+  };
   Pair<C> yh{}, yhm{}, ye{}, zh{}, zhm{}, ze{}, xh{}, xhm{}, xe{};
-  Prof<C> yph{}, ype{}, zph{}, zpe{}, zpm{}, xph{C(0), C(0), C(1), C(0)}, xpe = xph;
+  Prof<C> yph{}, ype{}, zph{}, zpe{}, zpm{}, xph{C(0), C(0), C(1)}, xpe = xph;
   if (iny) {
     yh = buf_ld<Pair<C>>(rpsi, vc, phin + yso(k));
     yhm = buf_ld<Pair<C>>(rpsi, below ? vc : kOut, phin + yso(km));
     ye = buf_ld<Pair<C>>(rpsi, own ? vc : kOut, yso(k));
-    yph = pf[4 * pl + jc];
-    ype = pf[pl + jc];
+    yph = profile(1, 1, jc);
+    ype = profile(0, 1, jc);
   }
   if (inz) {
     zh = buf_ld<Pair<C>>(rpsi, vc, phin + zso(k));
     ze = buf_ld<Pair<C>>(rpsi, own ? vc : kOut, zso(k));
-    zph = pf[5 * pl + k];
-    zpe = pf[2 * pl + k];
+    zph = profile(1, 2, k);
+    zpe = profile(0, 2, k);
   }
   if (inzm) {
     zhm = buf_ld<Pair<C>>(rpsi, vc, phin + zso(km));
-    zpm = pf[5 * pl + km];
+    zpm = profile(1, 2, km);
   }
   if (inx) {
     xh = buf_ld<Pair<C>>(rpsi, vx, phin + xso(k));
     xhm = buf_ld<Pair<C>>(rpsi, below ? vx : kOut, phin + xso(km));
     xe = buf_ld<Pair<C>>(rpsi, own ? vx : kOut, xso(k));
-    xph = pf[3 * pl + i];
-    xpe = pf[i];
+    xph = profile(1, 0, i);
+    xpe = profile(0, 0, i);
   }
   const Coef2<C> cf = buf_ld<Coef2<C>>(rcoef, (own && lane_ok) ? (bx + by * (uint32_t)a.nsx + bz * (uint32_t)a.nsxy) * (uint32_t)sizeof(Coef2<C>) : kOut, 0);
   uint32_t pm = 0u;

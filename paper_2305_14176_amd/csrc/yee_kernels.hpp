@@ -71,12 +71,6 @@ struct Coef2 {
   C ca, cb;
 };
 
-// CPML profile of one sample
-template <class C>
-struct alignas(4 * sizeof(C)) Prof {
-  C omb, a, kinv, pad;   // 1 - b, a, 1/kappa
-};
-
 // Kernel arguments.  Few base pointers (element offsets are derived in the
 // kernel) keep the scalar register file from spilling.
 template <class T, class C>
@@ -91,8 +85,7 @@ struct StepArgs {
   const C* psh_in;          // H-side psi, old
   C* psh_out;               // H-side psi, new
   uint32_t psoff[6];        // element offset of the pair array holding each psi auxiliary
-  const C* prof;            // CPML profiles [side E,H][axis][1 - b | a | 1/kappa][plen]
-  const Prof<C>* prof4;     // the same by sample: [side E,H][axis][plen]
+  const C* prof;            // CPML profiles by sample [side E,H][axis][plen][1 - b, a, 1/kappa]
   int32_t plen;
   const int32_t* seg;       // block index per cell: x [px] | y [ny] | z [nz]
   const Coef2<C>* coef;     // (Ca, Cb) per block [nsz][nsy][nsx]
@@ -431,7 +424,7 @@ __device__ __forceinline__ void step_tile(const StepArgs<T, C>& a, const int yti
 #pragma unroll
     for (int u = 0; u < 6; ++u) {
       const int side = u / 3, qq = u % 3;
-      tzp[u * nk1 + q] = inz ? a.prof[((side * 3 + 2) * 3 + qq) * a.plen + k] : (qq == 2 ? C(1) : C(0));
+      tzp[u * nk1 + q] = inz ? a.prof[((side * 3 + 2) * a.plen + k) * 3 + qq] : (qq == 2 ? C(1) : C(0));
     }
     tzs[q] = a.seg[px + ny + k] * a.nsxy;
     tzl[q] = a.pec_plane[k];
@@ -440,14 +433,14 @@ __device__ __forceinline__ void step_tile(const StepArgs<T, C>& a, const int yti
     const int u = q / RL, i = q - u * RL;
     const int side = u / 3, qq = u % 3;
     const bool inx = i < nx && (i < Lx || i >= nx - Lx);
-    txp[q] = inx ? a.prof[((side * 3 + 0) * 3 + qq) * a.plen + i] : (qq == 2 ? C(1) : C(0));
+    txp[q] = inx ? a.prof[((side * 3 + 0) * a.plen + i) * 3 + qq] : (qq == 2 ? C(1) : C(0));
   }
   for (int q = tid; q < 6 * (ty + 1); q += nthr) {
     const int u = q / (ty + 1), rr = q - u * (ty + 1);
     const int side = u / 3, qq = u % 3;
     const int jj = j0 - 1 + rr;
     const bool iny = jj >= 0 && jj < ny && (jj < Ly || jj >= ny - Ly);
-    typ[q] = iny ? a.prof[((side * 3 + 1) * 3 + qq) * a.plen + jj] : (qq == 2 ? C(1) : C(0));
+    typ[q] = iny ? a.prof[((side * 3 + 1) * a.plen + jj) * 3 + qq] : (qq == 2 ? C(1) : C(0));
   }
   for (int q = tid; q < (ty + 1) * nk; q += nthr) {
     const int rr = q / nk, kk = q - rr * nk;

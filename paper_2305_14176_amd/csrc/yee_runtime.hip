@@ -97,7 +97,7 @@ struct yee_ctx {
   bool bound = false;
   unsigned char* ws = nullptr;
   int64_t ws_bytes = 0;
-  Region fields[2], psi_e[2], psi_h[2], series, dft, stat, segr, coef, prof, prof4, pecplane, pecmask, rowflag,
+  Region fields[2], psi_e[2], psi_h[2], series, dft, stat, segr, coef, prof, pecplane, pecmask, rowflag,
       srcr, prober, freqr;
   size_t comp_bytes = 0;   // one component array
   size_t psi_len[6] = {};  // elements of each psi array (same for E and H side)
@@ -206,7 +206,6 @@ void layout(yee_ctx* c) {
   take(c->srcr, c->src.size() * sizeof(yee::SrcDev));
   take(c->prober, np * sizeof(int4));
   take(c->freqr, nf * sizeof(double));
-  take(c->prof4, 2 * 3 * 4 * c->prof_len * c->csize);
   c->ws_bytes = (int64_t)off;
 }
 
@@ -309,7 +308,6 @@ yee::StepArgs<T, C> fill_args(const yee_ctx* c, int V, int ty, int kz, bool reco
   a.psh_out = reinterpret_cast<C*>(c->ws + c->psi_h[nxt].off);
   for (int q = 0; q < 6; ++q) a.psoff[q] = c->psi_off[q];
   a.prof = reinterpret_cast<const C*>(c->ws + c->prof.off);
-  a.prof4 = reinterpret_cast<const Prof<C>*>(c->ws + c->prof4.off);
   a.plen = (int32_t)c->prof_len;
   a.seg = reinterpret_cast<const int32_t*>(c->ws + c->segr.off);
   a.coef = reinterpret_cast<const Coef2<C>*>(c->ws + c->coef.off);
@@ -1104,7 +1102,7 @@ yee_status yee_reset(yee_ctx* c, void* stream) {
   yee_status st = upload_materials_impl(c, s);
   if (st) return st;
   // CPML profiles
-  std::vector<unsigned char> pbuf(c->prof.bytes, 0), pbuf4(c->prof4.bytes, 0);
+  std::vector<unsigned char> pbuf(c->prof.bytes, 0);
   const int n3[3] = {d.nx, d.ny, d.nz};
   const double dw[3] = {d.dx, d.dy, d.dz};
   for (int side = 0; side < 2; ++side)
@@ -1112,21 +1110,14 @@ yee_status yee_reset(yee_ctx* c, void* stream) {
       std::vector<double> b, a, k;
       cpml_profile(d, dw[ax], c->dt, n3[ax], d.cpml_cells[ax], side, b, a, k);
       b.resize(c->prof_len, 0.0); a.resize(c->prof_len, 0.0); k.resize(c->prof_len, 1.0);
-      const size_t base = ((size_t)(side * 3 + ax) * 3) * c->prof_len * c->csize;
-      if (c->csize == 8) {
-        put<double>(pbuf, base, b); put<double>(pbuf, base + c->prof_len * 8, a); put<double>(pbuf, base + 2 * c->prof_len * 8, k);
-      } else {
-        put<float>(pbuf, base, b); put<float>(pbuf, base + c->prof_len * 4, a); put<float>(pbuf, base + 2 * c->prof_len * 4, k);
-      }
-      std::vector<double> by_sample(4 * c->prof_len, 0.0);
+      std::vector<double> by_sample(3 * c->prof_len);
       for (size_t q = 0; q < c->prof_len; ++q) {
-        by_sample[4 * q] = b[q]; by_sample[4 * q + 1] = a[q]; by_sample[4 * q + 2] = k[q];
+        by_sample[3 * q] = b[q]; by_sample[3 * q + 1] = a[q]; by_sample[3 * q + 2] = k[q];
       }
-      const size_t base4 = (size_t)(side * 3 + ax) * 4 * c->prof_len * c->csize;
-      if (c->csize == 8) put<double>(pbuf4, base4, by_sample); else put<float>(pbuf4, base4, by_sample);
+      const size_t base = (size_t)(side * 3 + ax) * 3 * c->prof_len * c->csize;
+      if (c->csize == 8) put<double>(pbuf, base, by_sample); else put<float>(pbuf, base, by_sample);
     }
   if ((st = upload(c, c->prof, pbuf.data(), pbuf.size(), s))) return st;
-  if ((st = upload(c, c->prof4, pbuf4.data(), pbuf4.size(), s))) return st;
   // PEC planes
   std::vector<int32_t> plane(d.nz, -1);
   std::vector<uint8_t> masks(c->pecmask.bytes, 0);

@@ -177,7 +177,7 @@ __device__ __forceinline__ void tb_tile(const StepArgs<T, C>& a, const int ytile
 #pragma unroll
     for (int u = 0; u < 6; ++u) {
       const int side = u / 3, qq = u % 3;
-      tzp[u * npl + q] = inz ? a.prof[((side * 3 + 2) * 3 + qq) * a.plen + k] : (qq == 2 ? C(1) : C(0));
+      tzp[u * npl + q] = inz ? a.prof[((side * 3 + 2) * a.plen + k) * 3 + qq] : (qq == 2 ? C(1) : C(0));
     }
     tzs[q] = ok ? a.seg[px + ny + k] * a.nsxy : 0;
     tzl[q] = ok ? a.pec_plane[k] : -1;
@@ -186,14 +186,14 @@ __device__ __forceinline__ void tb_tile(const StepArgs<T, C>& a, const int ytile
     const int u = q / RL, i = q - u * RL;
     const int side = u / 3, qq = u % 3;
     const bool inx = i < nx && (i < Lx || i >= nx - Lx);
-    txp[q] = inx ? a.prof[((side * 3 + 0) * 3 + qq) * a.plen + i] : (qq == 2 ? C(1) : C(0));
+    txp[q] = inx ? a.prof[((side * 3 + 0) * a.plen + i) * 3 + qq] : (qq == 2 ? C(1) : C(0));
   }
   for (int q = tid; q < 6 * NW; q += nthr) {
     const int u = q / NW, rr = q - u * NW;
     const int side = u / 3, qq = u % 3;
     const int jj = j0 - 2 + rr;
     const bool iny = jj >= 0 && jj < ny && (jj < Ly || jj >= ny - Ly);
-    typ[q] = iny ? a.prof[((side * 3 + 1) * 3 + qq) * a.plen + jj] : (qq == 2 ? C(1) : C(0));
+    typ[q] = iny ? a.prof[((side * 3 + 1) * a.plen + jj) * 3 + qq] : (qq == 2 ? C(1) : C(0));
   }
   for (int q = tid; q < NW * nq; q += nthr) {
     const int rr = q / nq, kk = q - rr * nq;
