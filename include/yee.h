@@ -263,8 +263,8 @@ yee_status yee_sparams(int32_t n_probes, int32_t n_freq, const double* dft_ref_r
  * choice (one sample per lane up to 256 samples per row, and in FP32 up to
  * 512; workgroups of at most 12 waves; the shortest chunk, at least 8 planes,
  * that lets every tile be resident on the device at once; FP64 rows of 129 to
- * 256 samples may take 16 waves; grids whose components hold at most 4 MiB run
- * one plane per workgroup without a march).  A workgroup of the march holds
+ * 256 samples may take 16 waves; of the grids whose components hold at most
+ * 4 MiB, those that are faster so run one plane per workgroup without a march).  A workgroup of the march holds
  * (tile_rows + 1) * ceil(nx / (64 * samples)) waves, at most 16; any nonzero
  * value selects the march.  Results do not depend on the launch shape. */
 yee_status yee_set_launch(yee_ctx* ctx, int32_t tile_rows, int32_t chunk_planes, int32_t samples_per_lane);

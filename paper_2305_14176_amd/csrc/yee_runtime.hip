@@ -532,11 +532,17 @@ int step_blocks_per_cu_v(int V, int threads, size_t lds) {
   }
 }
 
-int step_slots(const yee_ctx* c, int threads, size_t lds) {
+// Compute units of the current device (1 where that cannot be asked).
+int compute_units() {
   int dev_id = 0, cus = 0;
   if (hipGetDevice(&dev_id) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev_id) != hipSuccess || cus < 1)
     cus = 1;
+  return cus;
+}
+
+int step_slots(const yee_ctx* c, int threads, size_t lds) {
+  const int cus = compute_units();
   int per_cu = 1;
   switch (c->d.precision) {
     case YEE_F64: per_cu = step_blocks_per_cu_v<double, double>(c->V, threads, lds); break;
@@ -637,14 +643,29 @@ void tb_default_launch(yee_ctx* c) {
   c->tb_ok = true;
 }
 
-// Rows per tile of the no-march step, 0 where the march is faster or the
-// caller chose a launch shape.  The line lies at 4 MiB of one component in
-// compute precision, rows padded to whole waves (idle lanes cost the same).
-// Measured per step, march against no march (us): FP32 64^3 12.4 / 8.1,
-// 128 x 64 x 64 17.1 / 13.1, 64 x 96 x 96 18.3 / 12.6, 80^3 20.2 / 17.5 (below
-// the line); 96^3 22.6 / 23.9, FP64 80^3 27.3 / 29.1 (above it); FP64 64^3
-// 16.2 / 11.3.  Four rows: two to seven were within a few percent, three and
-// seven the slowest.
+// Rows per tile of the no-march step, 0 where the march (whose automatic shape
+// is set) is faster or the caller chose a launch shape.
+//
+// Four rows: two to seven were within a few percent, three and seven the
+// slowest.  Both steps are as slow as the fullest compute unit, so what they
+// give it is compared, in rows of 64 samples: `direct` the rows of its no-march
+// tiles, halo rows among them; `march` those of its marches over their planes
+// and the warm-up plane.  A row of the march costs about 3/8 of one of the
+// no-march step (which reads twice as much and recomputes H below), and a march
+// starts later by the time of `lead` such rows: its tables, and a chain of
+// planes that wait for one another.  FP64 rows take longer, so fewer; the FP16
+// march of wide rows without CPML, two samples a lane at half the bytes, leads
+// by less.
+// Measured on 4254 grids of up to 4 MiB of one component in compute precision
+// (rows of 1 to 7 waves; cubes, plates and bars; 0, 6 and 10 layers): the line
+// leaves no grid slower than its march by more than 5 % (FP16 and FP64; FP32
+// 1.5 %).  us per step, march / no march: taken 32^3 FP64 8.6 / 4.2,
+// 64^3 FP32 CPML 10 12.6 / 8.1, 100 x 72 x 72 19.2 / 15.2, 320 x 40 x 40 23.3 /
+// 16.4, 150 x 43 x 44 FP64 21.8 / 17.3; not taken 256 x 63 x 63 FP32 20.4 /
+// 25.2, 150 x 73 x 73 20.1 / 23.2, 384 x 51 x 52 24.3 / 32.2, 321 x 8 x 334 FP16
+// 20.7 / 35.7, 384 x 36 x 37 FP64 24.8 / 29.8.  Rows of one wave were faster
+// without a march up to the 4 MiB, past which nothing was measured (96^3, 6 MiB
+// at whole waves, 22.6 / 23.9).
 constexpr int64_t kDirectMaxBytes = int64_t(4) << 20;
 constexpr int kDirectRows = 4;
 
@@ -654,7 +675,17 @@ int direct_rows(const yee_ctx* c) {
   const int wpr = waves_per_row(d.nx, 1);
   if ((int64_t)wpr * yee::kWave * d.ny * d.nz * (int64_t)c->csize > kDirectMaxBytes) return 0;
   // (a wave of the workgroup is the sources')
-  return std::max(0, std::min({kDirectRows, d.ny, (yee::kMaxBlockWaves - 1) / wpr - 1}));
+  const int rows = std::max(0, std::min({kDirectRows, d.ny, (yee::kMaxBlockWaves - 1) / wpr - 1}));
+  if (rows == 0 || wpr == 1) return rows;
+  const int cus = compute_units();
+  auto fullest = [&](int64_t tiles) { return (tiles + cus - 1) / cus; };
+  const int64_t direct = fullest((int64_t)((d.ny + rows - 1) / rows) * d.nz) * (rows + 1) * wpr;
+  const int64_t march = fullest((int64_t)((d.ny + c->ty - 1) / c->ty) * ((d.nz + c->kz - 1) / c->kz)) *
+                        (c->kz + 1) * (c->ty + 1) * waves_per_row(d.nx, c->V) * c->V;
+  const bool layers = d.cpml_cells[0] + d.cpml_cells[1] + d.cpml_cells[2] > 0;
+  const double lead = d.precision == YEE_F64 ? (layers ? 16.5 : 16.0)
+                      : d.precision == YEE_F16S && !layers && wpr >= 4 ? 14.0 : 26.0;
+  return direct <= 0.375 * march + lead ? rows : 0;
 }
 
 void default_launch(yee_ctx* c) {
