@@ -1280,18 +1280,25 @@ rmd_status helper_stream(hipStream_t* out) {
 //
 // Before them the call's hits are resolved and, where n_tables > 0, its tables
 // computed: by prep_kernel, or in a call of one small batch (kInlineWork
-// rays x chirps) by the geometry kernel itself.  A ray then resolves its hits
-// once per chirp, which costs less than the launch up to about that size: us
-// per call, own launch and inline, 5003 rays x 8 chirps 22.5 / 21.1,
-// 5003 x 4 20.7 / 18.3, 100000 x 8 59.8 / 62.2, 300000 x 8 133 / 143.  (Before
-// prep_kernel, five launches: 28.6, 27.0, 69.6 and 146.)
+// rays x chirps) of rays with few hits (kInlineHits on average) by the geometry
+// kernel itself.  A ray then resolves its hits once per chirp, four loads that
+// wait for one another in place of two, which costs less than the launch up to
+// about that size: us per call, own launch and inline, 5003 rays x 8 chirps
+// 22.5 / 21.1, 5003 x 4 20.7 / 18.3, 100000 x 8 59.8 / 62.2, 300000 x 8 133 /
+// 143.  By hits a ray, 16000 rays x 4 chirps 1: 20.1 / 17.3, 6: 25.0 / 22.4, 16:
+// 35.0 / 34.4, 32: 53 / 75; 65000 x 4 6: 45.7 / 40.4, 12: 72 / 97, 32: 179 / 565;
+// 300 x 16 by the direct method 6: 18.3 / 18.1, 8: 19.9 / 20.6, 32: 36 / 47.  (The
+// host knows the mean alone: where one ray in 61 has 16 hits and the others two,
+// 300 x 16 takes 22.1 / 25.4, and 45 / 65 where it has 64.)
 constexpr int64_t kInlineWork = int64_t(1) << 18;
+constexpr int64_t kInlineHits = 6;
 
 template <class Work>
 rmd_status run_batches(const Plan& p, rmd::SynthArgs a, int32_t chirp0, int32_t chirp_count, int n_rays,
                        int n_tables, hipStream_t stream, Work&& work) {
     const int ray_blocks = (n_rays + rmd::kPrepThreads - 1) / rmd::kPrepThreads;
-    const bool inline_prep = chirp_count <= p.batch && (int64_t)n_rays * chirp_count <= kInlineWork;
+    const bool inline_prep = chirp_count <= p.batch && (int64_t)n_rays * chirp_count <= kInlineWork &&
+                             a.n_hits <= kInlineHits * n_rays;
     if (!inline_prep) {
         const int hit_blocks = (int)((a.n_hits + rmd::kPrepThreads - 1) / rmd::kPrepThreads);
         if (hit_blocks + n_tables > 0)
