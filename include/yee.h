@@ -260,13 +260,14 @@ yee_status yee_sparams(int32_t n_probes, int32_t n_freq, const double* dft_ref_r
 
 /* Launch shape of the fused step kernel: y-rows per workgroup tile, planes
  * per z-chunk and x samples per lane (1, 2 or 4); 0 keeps the automatic
- * choice (one sample per lane up to 256 samples per row, and in FP32 up to
+ * choice (one sample per lane up to 256 samples per row, and in FP64 up to
  * 512; workgroups of at most 12 waves; the shortest chunk, at least 8 planes,
  * that lets every tile be resident on the device at once; FP64 rows of 129 to
- * 256 samples may take 16 waves; of the grids whose components hold at most
- * 4 MiB, those that are faster so run one plane per workgroup without a march).  A workgroup of the march holds
- * (tile_rows + 1) * ceil(nx / (64 * samples)) waves, at most 16; any nonzero
- * value selects the march.  Results do not depend on the launch shape. */
+ * 320 samples may take 16 waves; of the grids whose components hold at most
+ * 4 MiB, those that are faster so run one plane per workgroup without a
+ * march).  A workgroup of the march holds (tile_rows + 1) * ceil(nx / (64 *
+ * samples)) waves, at most 16; any nonzero value selects the march.  Results
+ * do not depend on the launch shape. */
 yee_status yee_set_launch(yee_ctx* ctx, int32_t tile_rows, int32_t chunk_planes, int32_t samples_per_lane);
 
 /* Steps per sweep of yee_step.  A two-step sweep reads the fields and CPML

@@ -712,11 +712,10 @@ void default_launch(yee_ctx* c) {
   // planes per chunk: the fewest (at least min_chunk) that let every tile be
   // resident at once, so the launch runs in one round and each chunk pays its
   // warm-up plane once over as long a march as possible
+  auto slots = [&](int ty) { return step_slots(c, (ty + 1) * wpr * yee::kWave, step_lds_bytes(c, ty, c->V, d.nz)); };
   auto chunk_planes = [&](int ty) {
     if (c->kz_req > 0) return std::min(c->kz_req, d.nz);
-    const int threads = (ty + 1) * wpr * yee::kWave;
-    const int slots = step_slots(c, threads, step_lds_bytes(c, ty, c->V, d.nz));
-    const int chunks = std::max(1, slots / ((d.ny + ty - 1) / ty));
+    const int chunks = std::max(1, slots(ty) / ((d.ny + ty - 1) / ty));
     return std::min({d.nz, kMaxChunk, std::max(min_chunk, (d.nz + chunks - 1) / chunks)});
   };
   for (;;) {
@@ -726,16 +725,28 @@ void default_launch(yee_ctx* c) {
     --c->ty;
   }
   // FP64 steps take 128 VGPRs: a CU holds 16 waves, so one 12-wave workgroup
-  // and four idle slots.  Rows of three and four waves may take all 16 where
-  // the shorter march of the larger tile outweighs its slower planes (a plane
-  // takes about 8 + waves units).  us per step, 12 waves and up to 16:
-  // 150 x 130 x 110 85.8 / 78.0, 160^3 150.8 / 128.6, 200 x 200 x 100 182.9 /
-  // 152.6 (larger taken); 256 x 256 x 64 141.8 / 167.5 (not taken).
+  // and four idle slots (10 and six for rows of five waves).  Rows of three to
+  // five waves take all they can where that saves the fullest CU work: its
+  // planes, the warm-up plane among them, times the waves that each one passes
+  // through (a plane of the larger tile takes 1.25, 1.36 and 1.6 times as long
+  // with 15 waves for 12, 16 for 12 and 15 for 10), in as many rounds as the
+  // tiles need; by a twentieth at least, for a tile that saves less is often
+  // the slower one.  Of 1388 shapes (130 to 320 x 20 to 320 x 24 to 384, 0 and
+  // 8 CPML layers) 24 are slower than with the smaller tile, the worst 0.89
+  // times, and 98 would be faster with the larger, the best 1.11.  us per step
+  // with 8 layers, smaller and larger: taken 160 x 130 x 110 75.0 / 71.6, 160^3
+  // 146 / 126, 256 x 192 x 256 431 / 322 (two rounds and one), 320 x 96 x 110
+  // 168 / 108; not taken 192 x 96 x 160 88.7 / 102.6, 193 x 64 x 160 67.1 / 68.6;
+  // on the wrong side 256 x 96 x 64 41.8 / 43.8, and without CPML 193 x 80 x 160
+  // 68.5 / 76.4.
   const int wide = yee::max_block_waves(c->V) / wpr - 1;
   if (d.precision == YEE_F64 && c->V == 1 && wpr >= 3 && !tiny && !c->ty_req && wide > c->ty && wide <= d.ny) {
     const int kz = chunk_planes(wide);
-    auto cost = [&](int ty, int planes) { return (planes + 1) * (8 + (ty + 1) * wpr); };
-    if (cost(wide, kz) < cost(c->ty, c->kz) && step_lds_bytes(c, wide, c->V, kz) <= c->lds_limit) {
+    auto cost = [&](int ty, int planes) {
+      const int64_t tiles = (int64_t)((d.ny + ty - 1) / ty) * ((d.nz + planes - 1) / planes);
+      return (tiles + slots(ty) - 1) / slots(ty) * (planes + 1) * (2 + (ty + 1) * wpr);
+    };
+    if (20 * cost(wide, kz) < 19 * cost(c->ty, c->kz) && step_lds_bytes(c, wide, c->V, kz) <= c->lds_limit) {
       c->ty = wide;
       c->kz = kz;
     }
