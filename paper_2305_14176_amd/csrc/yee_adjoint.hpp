@@ -155,8 +155,9 @@ adj_h_kernel(const AdjArgs<C, C> a) {
   const C* pr = a.prof;
   const int pl = a.plen;
 
-  // (The profile loads come first in each layer: left to the scheduler they are
-  // issued after a wait for the auxiliaries, 26.4 instead of 24.9 us at 128^3 FP32.)
+  // (In the y and x layers, whose profile is read per lane, its load is held in
+  // front: left to the scheduler it is issued after a wait for the auxiliaries,
+  // 26.4 instead of 24.9 us at 128^3 FP32.)
   // dbar of the y terms (XY: +Ex, ZY: -Ez) at E samples j and j + 1
   C dxy0 = ux, dxy1 = ux_y, dzy0 = -uz, dzy1 = -uz_y;
   if (in_layer(j, ny, Ly)) {
@@ -178,14 +179,12 @@ adj_h_kernel(const AdjArgs<C, C> a) {
   if (in_layer(k, nz, Lz)) {
     const uint32_t q = ((uint32_t)slab(k, nz, Lz) * ny + j) * px + i;
     const C kv = pr[3 * (2 * pl + k) + 2], av = pr[3 * (2 * pl + k) + 1];
-    __builtin_amdgcn_sched_barrier(0);
     dyz0 = kv * uy + av * (P[a.psoff[PEYZ] + 2 * q + psi_member(PEYZ)] + uy);
     dxz0 = -kv * ux + av * (P[a.psoff[PEXZ] + 2 * q + psi_member(PEXZ)] - ux);
   }
   if (zp && in_layer(k + 1, nz, Lz)) {
     const uint32_t q = ((uint32_t)slab(k + 1, nz, Lz) * ny + j) * px + i;
     const C kv = pr[3 * (2 * pl + k + 1) + 2], av = pr[3 * (2 * pl + k + 1) + 1];
-    __builtin_amdgcn_sched_barrier(0);
     dyz1 = kv * uy_z + av * (P[a.psoff[PEYZ] + 2 * q + psi_member(PEYZ)] + uy_z);
     dxz1 = -kv * ux_z + av * (P[a.psoff[PEXZ] + 2 * q + psi_member(PEXZ)] - ux_z);
   }
@@ -287,14 +286,12 @@ adj_e_kernel(const AdjArgs<T, C> a) {
   if (in_layer(k, nz, Lz)) {
     const uint32_t q = ((uint32_t)slab(k, nz, Lz) * ny + j) * px + i;
     const C kv = pr[3 * (5 * pl + k) + 2], av = pr[3 * (5 * pl + k) + 1];
-    __builtin_amdgcn_sched_barrier(0);
     gyz1 = -mu * kv * hy + av * (Q[a.psoff[PHYZ] + 2 * q + psi_member(PHYZ)] - mu * hy);
     gxz1 = mu * kv * hx + av * (Q[a.psoff[PHXZ] + 2 * q + psi_member(PHXZ)] + mu * hx);
   }
   if (zm && in_layer(k - 1, nz, Lz)) {
     const uint32_t q = ((uint32_t)slab(k - 1, nz, Lz) * ny + j) * px + i;
     const C kv = pr[3 * (5 * pl + k - 1) + 2], av = pr[3 * (5 * pl + k - 1) + 1];
-    __builtin_amdgcn_sched_barrier(0);
     gyz0 = -mu * kv * hy_z + av * (Q[a.psoff[PHYZ] + 2 * q + psi_member(PHYZ)] - mu * hy_z);
     gxz0 = mu * kv * hx_z + av * (Q[a.psoff[PHXZ] + 2 * q + psi_member(PHXZ)] + mu * hx_z);
   }
