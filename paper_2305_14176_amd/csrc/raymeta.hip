@@ -816,11 +816,12 @@ __global__ void reduce_kernel(const float2* __restrict__ partial, float2* __rest
 // exchange through LDS, log8 L - 1 times.  Twiddles exp(-2 pi i k / L), k < L/2,
 // are formed in FP64 and rounded once, after the loads are under way.
 //
-// What bounds it is latency, not the 16 bytes per sample of traffic: a radix-2
-// transform in LDS paid two barriers and two LDS round trips for each of its
-// log2 L stages and started from bit-reversed LDS writes.  12 x 128 x 512
-// samples took 35 us for both passes of that and take 12 here, 12 x 512 x 1024
-// 133 and 46 (2.2 TB/s); calls of 12 us are bound by the host.
+// What bounds it is latency, not the 16 bytes per sample and pass of traffic: a
+// radix-2 transform in LDS paid two barriers and two LDS round trips for each of
+// its log2 L stages and started from bit-reversed LDS writes.  12 x 128 x 512
+// samples took 35 us for both passes of that and take 11.5 here (6.3 and 5.0 us
+// of kernel: the loads, the FP64 twiddles, two exchanges and the stores one after
+// another), 12 x 512 x 1024 133 and 46 (4.4 TB/s over both).
 //
 // STRIDED: the elements of a line are 2^lg apart and lines m, m + 1, ... are
 // neighbours in memory (2^lg of them a group): lanes run over the lines, and the
@@ -1022,7 +1023,8 @@ rmd_status check_scene_desc(const rmd_scene* sc) {
 // geometry (7 doubles per ray and chirp) fits in kGeoBudget bytes, at most
 // kMaxBatch chirps.  Within a batch the rays are split into partitions so that
 // the (pair, chirp, partition) workgroups fill the device several times over,
-// each wave keeping at least four 64-ray super-groups.  The workspace holds the
+// each of four waves keeping at least four 64-ray super-groups (two, where the
+// spreading takes eight waves a workgroup).  The workspace holds the
 // batch's geometry, then the partition results of either method (direct:
 // n_samples complex values per block; spreading: an M-cell grid per block and
 // the deconvolution table), so one size serves both entry points.

@@ -16,7 +16,8 @@
 //
 // Measured per step against the march (us): 32^3 FP64 without CPML 8.8 -> 4.0,
 // 12 x 12 x 140 FP32 8.5 -> 4.1, 32^3 FP32 with CPML 8 11.1 -> 4.0, 64^3 FP32
-// 12.3 -> 8.0, 96^3 22.7 -> 26.4 (direct_rows in yee_runtime.hip draws the line).
+// 12.9 -> 8.5, 80^3 20.3 -> 17.2, 96^3 22.8 -> 23.5, 128^3 33 -> 41 (direct_rows
+// in yee_runtime.hip draws the line).
 #pragma once
 
 #include "yee_kernels.hpp"

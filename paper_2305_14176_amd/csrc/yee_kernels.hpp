@@ -283,12 +283,18 @@ struct Raw<8> {
   }
 };
 // A 16-byte store reads its data registers over several cycles, the last
-// lanes' last.  With the uniform offset in a scalar register the compiler
-// takes no wait state before the next vector instruction may overwrite them;
-// on gfx950 that instruction then reaches memory in lanes 60-63, now and then
-// (seen as wrong auxiliaries in an FP64 step where a select follows the store
-// directly).  The data registers are therefore held until
-// after a wait state.
+// lanes' last, and asks for wait states before a vector instruction overwrites
+// them.  The published instruction set manuals exempt the form whose uniform
+// offset is in a scalar register, and the compiler takes none there.  On gfx950
+// such an instruction was seen to reach memory in lanes 60-63, now and then
+// (wrong auxiliaries in an FP64 step where a select follows the store
+// directly): an observation, not a published rule.  The data registers are
+// therefore held until after the two wait states that the other form gets.
+// Only FP64 auxiliaries and rows of four FP32 or two FP64 samples a lane are
+// stored so; 256^3 FP64 with CPML takes 473 us a step for 455 without the hold.
+// With the offset in the address register (the compiler then waits by itself)
+// it is 7 % slower still, by two 8-byte stores 11 %: the march is short of
+// registers.
 __device__ __forceinline__ void hold_store_data(u32x4 v) { asm volatile("s_nop 1" ::"v"(v)); }
 template <>
 struct Raw<16> {

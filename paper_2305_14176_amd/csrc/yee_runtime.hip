@@ -552,11 +552,6 @@ int step_slots(const yee_ctx* c, int threads, size_t lds) {
   return per_cu * cus;
 }
 
-// Samples per lane: one while a row fits in four waves; wider rows (up to
-// eight waves) keep one sample per lane in FP32 and take two otherwise (with
-// 2-byte storage one-sample loads would be half-width).  Measured at
-// 512 x 512 x 256: FP32 1.04 ms per step with one sample, 1.35 with two;
-// FP16 storage 1.08 with two, 1.10 with one.
 // Samples per lane when the caller does not choose: one up to 256-sample rows;
 // past that two for FP32 and FP16 storage (512 x 512 x 256: 0.88 against
 // 1.10 ms in FP32, 0.69 against 1.01 ms in FP16 storage), but one for FP64,
@@ -692,12 +687,14 @@ void default_launch(yee_ctx* c) {
   const auto& d = c->d;
   c->V = c->vpl ? c->vpl : default_samples_per_lane(d);
   const int wpr = waves_per_row(d.nx, c->V);
-  // Small grids: a step's time is the march of one chunk (its planes run one
-  // after another), not bandwidth, so they take shorter chunks and, up to
-  // 2^18 cells, at most two rows per tile, for more workgroups in flight.
-  // Measured per step: 12 x 12 x 140 16.8 -> 8.9 us, 32^3 21.1 -> 10.0 us,
-  // 64^3 21.6 -> 12.6 us (two rows, two-plane chunks); 96^3 25.7 -> 22.4 us
-  // (four-plane chunks; two-plane chunks were slower there, 37.8 us).
+  // Small grids: a march's time is that of one chunk (its planes run one after
+  // another), not bandwidth, so they take shorter chunks and, up to 2^18 cells,
+  // at most two rows per tile, for more workgroups in flight.  Measured per
+  // marched step: 12 x 12 x 140 16.8 -> 8.9 us, 32^3 21.1 -> 10.0 us, 64^3 21.6
+  // -> 12.6 us (two rows, two-plane chunks); 96^3 25.7 -> 22.4 us (four-plane
+  // chunks; two-plane chunks were slower there, 37.8 us).  Most of these grids
+  // take the step without a march (direct_rows, which weighs this shape against
+  // it); wide rows and the larger of them march.
   const int64_t cells = (int64_t)d.nx * d.ny * d.nz;
   const bool tiny = cells <= (int64_t(1) << 18);
   const int min_chunk = tiny ? 2 : (cells <= (int64_t(1) << 20) ? 4 : kMinChunk);
