@@ -723,35 +723,17 @@ __global__ __launch_bounds__(THREADS) void spread_kernel(SynthArgs a) {
     }
 }
 
-// Sum over n values `stride` apart, in FP64 and in order; eight loads in flight
-// at a time, then four.  Loaded one after another, 43 partitions of 12 pairs x
-// 16 chirps x 512 samples took reduce_kernel 13 us, now 6.
-__device__ inline void sum_parts(const float2* __restrict__ src, int64_t stride, int n, double& re, double& im) {
-    re = im = 0.0;
-    int p = 0;
-    for (; p + 8 <= n; p += 8) {
-        float2 v[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) v[c] = src[(p + c) * stride];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            re += v[c].x;
-            im += v[c].y;
-        }
-    }
-#pragma unroll 4
-    for (; p < n; ++p) {
-        const float2 v = src[p * stride];
-        re += v.x;
-        im += v.y;
-    }
-}
-
 // Workgroup (pair q, batch chirp j): the partitions' grids of the block summed
 // in FP64 in partition order, loaded bit-reversed; the inverse DFT
 // G[m] = sum_l g[l] e^{2 pi i m l / M} by radix-2 decimation in time in FP64
 // in LDS (twiddles from sincospi); then s[n] = G[(n - center) mod M] deconv[n]
 // rounded once to float32 and written into the cube at chirp c0 + j.
+//
+// Bound by instructions, not by the sums' loads: they are mostly few, and the
+// set-up of a loop with eight loads in flight costs each of the 16 waves more
+// than its loads save.  us with four loads / with eight: 3072 blocks of one
+// partition 43.5 / 66.5, 192 of one 6.9 / 7.4, 192 of 43 14.0 / 14.5, one of
+// 146 18.9 / 20.2.
 constexpr int kFinishThreads = 1024;     // one grid cell per thread at M = 1024
 
 __global__ __launch_bounds__(kFinishThreads) void finish_kernel(SynthArgs a, float2* __restrict__ s, int n_chirps_out,
@@ -769,8 +751,13 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(SynthArgs a, flo
     const int64_t stride = (int64_t)a.n_pairs * a.chirp_count * L;
     const float2* src = a.partial + ((int64_t)q * a.chirp_count + jj) * L;
     for (int l = threadIdx.x; l < L; l += blockDim.x) {
-        double re, im;
-        sum_parts(src + l, stride, a.n_parts, re, im);
+        double re = 0.0, im = 0.0;
+#pragma unroll 4
+        for (int p = 0; p < a.n_parts; ++p) {
+            const float2 v = src[(int64_t)p * stride + l];
+            re += v.x;
+            im += v.y;
+        }
         x[__brev((unsigned)l) >> (32 - logL)] = make_double2(re, im);
     }
     __syncthreads();
@@ -795,13 +782,33 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(SynthArgs a, flo
     }
 }
 
+// Sample i of the cube: its partitions' values summed in FP64 and in order,
+// eight loads in flight at a time, then four.  Bound by the latency of that
+// chain.  us with four loads / with eight: 43 partitions of 98304 samples
+// 13.5 / 6.2, 146 of 300 samples 29.0 / 7.5; 8 or fewer the same.
 __global__ void reduce_kernel(const float2* __restrict__ partial, float2* __restrict__ s, int n_pairs, int nb,
                               int n_samples, int n_parts, int n_chirps_out, int c0) {
     const int64_t count = (int64_t)n_pairs * nb * n_samples;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= count) return;
-    double re, im;
-    sum_parts(partial + i, count, n_parts, re, im);
+    double re = 0.0, im = 0.0;
+    int p = 0;
+    for (; p + 8 <= n_parts; p += 8) {
+        float2 v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = partial[(p + c) * count + i];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            re += v[c].x;
+            im += v[c].y;
+        }
+    }
+#pragma unroll 4
+    for (; p < n_parts; ++p) {
+        const float2 v = partial[p * count + i];
+        re += v.x;
+        im += v.y;
+    }
     const int n = (int)(i % n_samples);
     const int64_t qj = i / n_samples;
     const int jj = (int)(qj % nb), q = (int)(qj / nb);
