@@ -461,7 +461,11 @@ __device__ inline void split2(float x, float y, uint32_t& hi, uint32_t& lo) {
 // accumulates one super-group (64 rays); super-group sums are added into a
 // second accumulator, which keeps the float32 sums short.  Waves combine through LDS in a fixed
 // order.
-__global__ __launch_bounds__(kThreads) void synth_kernel(SynthArgs a) {
+//
+// SIMD_WAVES: waves a SIMD, and workgroups a CU, that the registers have to
+// leave room for: at 4 the kernel keeps within 128, at 3 it takes 132.
+template <int SIMD_WAVES>
+__global__ __launch_bounds__(kThreads, SIMD_WAVES) void synth_kernel(SynthArgs a) {
     __shared__ uint4 lds_raw[kWaves * kTableWords / 4];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1425,6 +1429,16 @@ void launch_spread_copies(const rmd::SynthArgs& a, dim3 grid, int M, int copies,
     else launch_spread_as<2, THREADS>(a, grid, M, stream);
 }
 
+// Four workgroups a CU where the launch has them: with up to three a CU (of 256)
+// all are resident either way, and the kernel is quicker with its registers.  us
+// per launch at 3 / 4 waves a SIMD: 6 workgroups 20.5 / 21.9, 192 16.4 / 17.5,
+// 768 37.2 / 38.0; 800 11.1 / 8.5, 1024 11.7 / 8.7, 3072 134 / 130, 6144 45.8 /
+// 40.6, 7680 323 / 304, 9600 60.3 / 52.4.
+void launch_synth(const rmd::SynthArgs& a, dim3 grid, hipStream_t stream) {
+    if (grid.x <= 3 * 256) hipLaunchKernelGGL((rmd::synth_kernel<3>), grid, dim3(rmd::kThreads), 0, stream, a);
+    else hipLaunchKernelGGL((rmd::synth_kernel<4>), grid, dim3(rmd::kThreads), 0, stream, a);
+}
+
 // Grid copies and threads of a spreading workgroup.  Copies spread the atomics
 // over the banks but are cleared and summed once per workgroup: about 2048
 // cells of them, and 4096 (with 512 threads, for the same LDS per wave) where a
@@ -1510,7 +1524,7 @@ rmd_status rmd_if_cube_direct(const rmd_scene* scene, const rmd_radar* radar, in
     return run_batches(p, a, chirp0, chirp_count, scene->n_rays, 0, stream,
                        [&](const rmd::SynthArgs& w, int nb, int c0) {
                            const dim3 grid((unsigned)((int64_t)n_pairs * w.n_passes * nb * p.parts));
-                           hipLaunchKernelGGL(rmd::synth_kernel, grid, dim3(rmd::kThreads), 0, stream, w);
+                           launch_synth(w, grid, stream);
                            const int64_t count = (int64_t)n_pairs * nb * n_samples;
                            hipLaunchKernelGGL(rmd::reduce_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
                                               stream, w.partial, reinterpret_cast<float2*>(s), n_pairs, nb, n_samples,
