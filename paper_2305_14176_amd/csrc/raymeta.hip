@@ -1450,9 +1450,18 @@ void launch_synth(const rmd::SynthArgs& a, dim3 grid, hipStream_t stream) {
 // 513 / 475; 256: 4352 333 / 354, 6144 456 / 453, 9472 655 / 656; 128: 9472
 // 615 / 603.  256 threads / 512: 8 and 16 workgroups a CU of M = 1024 147.5 /
 // 154.7, one a CU 22.4 / 20.9; M = 2048 176 / 167.
+//
+// Fewer than 1024 rays are a single partition, too short to pay for as much:
+// about 1024 cells, 512 below 96 rays, and 8 copies at most.  Time per call
+// relative to 2 copies, 4 / 8 / 16, 9600 workgroups: M = 64: 64 rays 0.98 / 0.98
+// / 1.09, 256 0.86 / 0.79 / 0.82, 1024 0.70 / 0.54 / 0.50; 128: 64 1.00 / 1.04 /
+// 1.30, 256 0.94 / 0.88 / 1.03, 1024 0.82 / 0.67 / 0.70; 256: 64 1.02 / 1.15 /
+// 1.74, 256 0.95 / 0.99 / 1.40, 1024 0.84 / 0.80 / 1.08; 512: 64 1.09, 256 1.04,
+// 1024 0.96 (4 copies).
 void launch_spread(const rmd::SynthArgs& a, dim3 grid, int M, int rays_per_part, hipStream_t stream) {
     const bool long_part = rays_per_part >= (M >= 512 ? 4096 : 8192);
-    const int copies = std::min(16, std::max(2, (long_part ? 4096 : 2048) / M));
+    const int cells = long_part ? 4096 : a.n_rays >= 1024 ? 2048 : a.n_rays >= 96 ? 1024 : 512;
+    const int copies = std::min(a.n_rays >= 1024 ? 16 : 8, std::max(2, cells / M));
     if (long_part || M >= 2048 || grid.x <= 256) launch_spread_copies<512>(a, grid, M, copies, stream);
     else launch_spread_copies<256>(a, grid, M, copies, stream);
 }

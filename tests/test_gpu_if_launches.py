@@ -1,6 +1,6 @@
 """Which launch an IF call takes, read from the kernel nodes of a captured call:
 four workgroups of synth_kernel a compute unit where the grid has more than three
-for each.
+for each, and fewer copies of the spreading grid for few rays.
 
 Results against the FP64 oracle: relative L2 <= 1e-5 per (pair, chirp) block, as
 for every IF cube (FP64 phases, FP32 phasors or 2^-29 fixed point: about 1e-6).
@@ -79,3 +79,18 @@ def test_direct_launch_fills_its_compute_units(n_rays, n_pairs, n_chirps, n_samp
     assert _hip().hipOccupancyMaxActiveBlocksPerMultiprocessor(C.byref(per_cu), C.c_void_p(k.func), 256,
                                                                C.c_size_t(k.lds)) == 0
     assert per_cu.value == (4 if k.grid.x > 3 * 256 else 3)
+
+
+@pytest.mark.parametrize("n_rays, n_samples, copies", [
+    (1, 30, 8), (95, 30, 8), (96, 30, 8), (1023, 30, 8), (1024, 30, 16),            # 64 cells
+    (95, 60, 4), (96, 60, 8), (1023, 60, 8), (1024, 60, 16),                        # 128
+    (95, 120, 2), (96, 120, 4), (1023, 120, 4), (1024, 120, 8),                     # 256
+    (95, 250, 2), (1023, 250, 2), (1024, 250, 4),                                   # 512
+    (95, 500, 2), (1024, 500, 2),                                                   # 1024
+])
+@pytest.mark.parametrize("n_pairs", [1, 20])                                        # 16 and 320 workgroups
+def test_spread_copies_follow_the_rays(n_pairs, n_rays, n_samples, copies):
+    k = _run("spread", n_rays, n_pairs, 16, n_samples)
+    cells = 1 << (2 * n_samples - 1).bit_length()
+    assert (k.grid.x, k.block.x) == (16 * n_pairs, 256 if n_pairs > 16 else 512)
+    assert k.lds == copies * 2 * (cells + 8) * 8
