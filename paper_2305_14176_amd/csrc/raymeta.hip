@@ -736,8 +736,8 @@ __global__ __launch_bounds__(THREADS) void spread_kernel(SynthArgs a) {
 // Bound by instructions, not by the sums' loads: they are mostly few, and the
 // set-up of a loop with eight loads in flight costs each of the 16 waves more
 // than its loads save.  us with four loads / with eight: 3072 blocks of one
-// partition 43.5 / 66.5, 192 of one 6.9 / 7.4, 192 of 43 14.0 / 14.5, one of
-// 146 18.9 / 20.2.
+// partition 43.5 / 66.5, 192 of one 6.9 / 7.4, 192 of 40 14.0 / 14.5, one of
+// 118 18.9 / 20.2.
 constexpr int kFinishThreads = 1024;     // one grid cell per thread at M = 1024
 
 __global__ __launch_bounds__(kFinishThreads) void finish_kernel(SynthArgs a, float2* __restrict__ s, int n_chirps_out,
@@ -788,8 +788,8 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(SynthArgs a, flo
 
 // Sample i of the cube: its partitions' values summed in FP64 and in order,
 // eight loads in flight at a time, then four.  Bound by the latency of that
-// chain.  us with four loads / with eight: 43 partitions of 98304 samples
-// 13.5 / 6.2, 146 of 300 samples 29.0 / 7.5; 8 or fewer the same.
+// chain.  us with four loads / with eight: 40 partitions of 98304 samples
+// 13.5 / 6.2, 118 of 300 samples 29.0 / 7.5; 8 or fewer the same.
 __global__ void reduce_kernel(const float2* __restrict__ partial, float2* __restrict__ s, int n_pairs, int nb,
                               int n_samples, int n_parts, int n_chirps_out, int c0) {
     const int64_t count = (int64_t)n_pairs * nb * n_samples;
